@@ -160,6 +160,33 @@ __device__ __forceinline__ uint32_t mulmod_2p31(uint32_t x, uint32_t a) {
   return t >= M ? t - M : t;
 }
 
+// a^e mod m and the affine map of J steps of a 48-bit LCG, for jump constants
+constexpr uint64_t cpowmod(uint64_t a, uint64_t e, uint64_t m) {
+  uint64_t r = 1 % m;
+  a %= m;
+  while (e) {
+    if (e & 1) r = r * a % m;
+    a = a * a % m;
+    e >>= 1;
+  }
+  return r;
+}
+
+struct Affine48 {
+  uint64_t a, c;
+};
+// J steps of X -> a X + c mod 2^48 as one affine map
+constexpr Affine48 caffine_pow(uint64_t a, uint64_t c, uint64_t J) {
+  constexpr uint64_t M = (1ull << 48) - 1;
+  Affine48 r{1, 0}, b{a & M, c & M};
+  while (J) {
+    if (J & 1) r = Affine48{(b.a * r.a) & M, (b.a * r.c + b.c) & M};
+    b = Affine48{(b.a * b.a) & M, (b.a * b.c + b.c) & M};
+    J >>= 1;
+  }
+  return r;
+}
+
 // --------------------------------------------------------------- sinks
 // The per-wave LDS stage of one chunk.  Draw j of lane l sits in slot
 // (j >> 1) * 130 + 2 l + (j & 1), so the two draws of a pair are adjacent and
@@ -234,14 +261,14 @@ struct StageSink {  // generation: draw j of the chunk goes to the wave's stage
   __device__ __forceinline__ void operator()(int j, uint32_t u) { st.put(lane, j, u); }
 };
 
-template <int BITS>
+template <int BITS, int PITCH = kPitch>
 struct FusedSink {  // in-kernel consumer: mantissa sum and 64-bin histogram
   uint32_t acc;
   uint32_t* hcol;
   __device__ __forceinline__ void operator()(int, uint32_t u) {
     uint32_t k = u >> (BITS - 24);
     acc += k;
-    __hip_atomic_fetch_add(&hcol[(k >> 18) * kPitch], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_fetch_add(&hcol[(k >> 18) * PITCH], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
   }
 };
 
@@ -271,6 +298,12 @@ struct Ggl {
     x = mulmod_2p31<1u>(st[si], jd[0]);
     return 0;
   }
+  // the map of q steps, for the host, and its application
+  static void q_map(uint64_t q, uint64_t& j0, uint64_t& j1) {
+    j0 = cpowmod(16807u, q, 2147483647u);
+    j1 = 0;
+  }
+  __device__ void advance(uint64_t j0, uint64_t) { x = mulmod_2p31<1u>(x, (uint32_t)j0); }
   template <bool PRED, class S>
   __device__ __forceinline__ void chunk(uint32_t lo, uint32_t vbeg, uint32_t vend, S& sink) {
 #pragma unroll
@@ -309,43 +342,47 @@ struct Xor128 {
   // row i (jd[4i..4i+3]) is the image of state bit i (bit i % 32 of word i / 32)
   __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd, const uint32_t*,
                                   uint32_t*) {
-    const uint32_t in[4] = {st[si], st[sn + si], st[2 * sn + si], st[3 * sn + si]};
-    uint32_t o[4] = {0u, 0u, 0u, 0u};
-#pragma unroll 8
-    for (int i = 0; i < 128; ++i) {
-      const uint32_t mask = 0u - ((in[i >> 5] >> (i & 31)) & 1u);
-      const v4u row = *reinterpret_cast<const v4u*>(jd + 4 * i);
-      o[0] ^= row.x & mask;
-      o[1] ^= row.y & mask;
-      o[2] ^= row.z & mask;
-      o[3] ^= row.w & mask;
-    }
-    x = o[0];
-    y = o[1];
-    z = o[2];
-    w = o[3];
+    uint32_t s[4] = {st[si], st[sn + si], st[2 * sn + si], st[3 * sn + si]};
+    matvec(s, jd);
+    x = s[0];
+    y = s[1];
+    z = s[2];
+    w = s[3];
     return 0;
+  }
+  // one product with a 128x128 GF(2) matrix in the row layout of load_jumped:
+  // every state bit costs its mask and one xor-and per word
+  __device__ static void matvec(uint32_t* s, const uint32_t* __restrict__ m) {
+    uint32_t o[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll 8
+      for (int i = 0; i < 32; ++i) {
+        const uint32_t mask = 0u - ((s[q] >> i) & 1u);
+        const v4u row = *reinterpret_cast<const v4u*>(m + 128 * q + 4 * i);
+        o[0] = __builtin_amdgcn_bitop3_b32(o[0], row.x, mask, kLutXorAnd);
+        o[1] = __builtin_amdgcn_bitop3_b32(o[1], row.y, mask, kLutXorAnd);
+        o[2] = __builtin_amdgcn_bitop3_b32(o[2], row.z, mask, kLutXorAnd);
+        o[3] = __builtin_amdgcn_bitop3_b32(o[3], row.w, mask, kLutXorAnd);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] = o[q];
+  }
+  __device__ void advance_by(const uint32_t* __restrict__ m) {
+    uint32_t s[4] = {x, y, z, w};
+    matvec(s, m);
+    x = s[0];
+    y = s[1];
+    z = s[2];
+    w = s[3];
   }
   // state E steps ahead of the one at `st`: one product with T^(2^k) from
   // the object's table for every set bit k of E (E uniform over the wave)
   __device__ void load_jumped_pow2(const uint32_t* st, uint64_t sn, uint64_t si, uint32_t E, const uint32_t* pow2) {
     uint32_t s[4] = {st[si], st[sn + si], st[2 * sn + si], st[3 * sn + si]};
-    for (int k = 0; k < kXorPow2; ++k) {
-      if (!((E >> k) & 1u)) continue;
-      const uint32_t* m = pow2 + 512 * k;
-      uint32_t o[4] = {0u, 0u, 0u, 0u};
-#pragma unroll 8
-      for (int i = 0; i < 128; ++i) {
-        const uint32_t mask = 0u - ((s[i >> 5] >> (i & 31)) & 1u);
-        const v4u row = *reinterpret_cast<const v4u*>(m + 4 * i);
-        o[0] ^= row.x & mask;
-        o[1] ^= row.y & mask;
-        o[2] ^= row.z & mask;
-        o[3] ^= row.w & mask;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) s[q] = o[q];
-    }
+    for (int k = 0; k < kXorPow2; ++k)
+      if ((E >> k) & 1u) matvec(s, pow2 + 512 * k);
     x = s[0];
     y = s[1];
     z = s[2];
@@ -392,6 +429,14 @@ struct Ranecu {
     s2 = mulmod_2p31<249u>(st[sn + si], jd[1]);
     return 0;
   }
+  static void q_map(uint64_t q, uint64_t& j0, uint64_t& j1) {
+    j0 = cpowmod(40014u, q, 2147483563u);
+    j1 = cpowmod(40692u, q, 2147483399u);
+  }
+  __device__ void advance(uint64_t j0, uint64_t j1) {
+    s1 = mulmod_2p31<85u>(s1, (uint32_t)j0);
+    s2 = mulmod_2p31<249u>(s2, (uint32_t)j1);
+  }
   template <bool PRED, class S>
   __device__ __forceinline__ void chunk(uint32_t lo, uint32_t vbeg, uint32_t vend, S& sink) {
 #pragma unroll
@@ -437,6 +482,16 @@ struct Lcg48 {
     x0 = (uint32_t)y;
     x1 = (uint32_t)(y >> 32) & 0xFFFFu;
     return 0;
+  }
+  static void q_map(uint64_t q, uint64_t& j0, uint64_t& j1) {
+    const Affine48 f = caffine_pow(A, C, q);
+    j0 = f.a;
+    j1 = f.c;
+  }
+  __device__ void advance(uint64_t j0, uint64_t j1) {
+    const uint64_t y = j0 * ((uint64_t)x0 | ((uint64_t)x1 << 32)) + j1;
+    x0 = (uint32_t)y;
+    x1 = (uint32_t)(y >> 32) & 0xFFFFu;
   }
   template <bool PRED, class S>
   __device__ __forceinline__ void chunk(uint32_t lo, uint32_t vbeg, uint32_t vend, S& sink) {

@@ -27,11 +27,6 @@ const char* last_error();
   } while (0)
 
 inline bool valid_kind(int k) { return k >= GGL && k < kKinds; }
-inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
-inline size_t state_region_bytes(int kind, uint64_t n) {
-  if (kind == MT19937) return align256(n * kMtStride * 4ull);
-  return align256(n * (uint64_t)kStateWords[kind] * 4ull);
-}
 
 struct DeviceGuard {
   int prev = -1;

@@ -110,6 +110,36 @@ struct TableTask {
   uint32_t pad;
 };
 
+// Layout of an object's device buffer: the state region; the seed tuples read
+// by the initialisation kernel and, for the kinds whose plain generation cuts
+// streams into jumped segments (RANLUX, XOR128), the snapshot the segments jump
+// from (the seed area is free again once the object exists); then the object's
+// jump tables, written once by prng_create: for RANLUX the 25
+// block-completion multipliers and the block-jump table of its luxury, for
+// XOR128 the powers T^(2^k).
+inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
+inline size_t state_region_bytes(int kind, uint64_t n) {
+  if (kind == MT19937) return align256(n * kMtStride * 4ull);
+  return align256(n * (uint64_t)kStateWords[kind] * 4ull);
+}
+inline bool splits(int kind) { return kind == RANLUX || kind == XOR128; }
+inline size_t scratch_bytes(int kind, uint64_t n) {
+  size_t b = n * kSeedWords[kind] * 8ull;
+  if (splits(kind) && b < state_region_bytes(kind, n)) b = state_region_bytes(kind, n);
+  return align256(b);
+}
+inline size_t table_bytes(int kind) {
+  if (kind == RANLUX) return align256((size_t)(kRanluxAuxWords + kLuxDigitWords) * 4);
+  if (kind == XOR128) return align256((size_t)kXorPow2Words * 4);
+  return 0;
+}
+inline uint32_t* snapshot_area(int kind, uint32_t* state, uint64_t n) {
+  return state + state_region_bytes(kind, n) / 4;
+}
+inline const uint32_t* object_tables(int kind, const uint32_t* state, uint64_t n) {
+  return state + (state_region_bytes(kind, n) + scratch_bytes(kind, n)) / 4;
+}
+
 // Device scratch of prng_generate_noalloc: a file-scope array of this many
 // bytes on every device; static_scratch gives its address on `device`, which
 // must be the current device (looked up once per device, then cached).
@@ -152,6 +182,8 @@ hipError_t launch_generate_packed(int kind, uint32_t p, uint32_t* state, uint64_
 // (where = 1) or in HBM (where = 2): the paper's other two implementations.
 hipError_t launch_ranlux_variant(int where, uint32_t p, uint32_t* state, uint64_t n, uint64_t draws, int dtype,
                                  void* out, uint64_t row_elems, uint64_t elem_off, hipStream_t s);
+// `state` is an object's state buffer: XOR128 takes its jump matrices from the
+// object's tables behind it.
 hipError_t launch_fused(int kind, uint32_t p, uint32_t* state, uint64_t n, uint64_t draws, uint64_t* sum,
                         uint32_t* hist, bool accumulate, hipStream_t s);
 // Start of a table run: zero n_counters task counters and copy the n

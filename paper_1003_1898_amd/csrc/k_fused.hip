@@ -1,4 +1,7 @@
 // In-kernel consumers: exact mantissa sums and 64-bin histograms per stream.
+#include <bit>
+#include <cmath>
+
 #include "device.h"
 
 namespace prng {
@@ -48,6 +51,97 @@ __global__ __launch_bounds__(256) void k_lane_fused(uint32_t* __restrict__ state
 #pragma unroll
     for (int b = 0; b < 64; ++b) hp[b] = (accumulate ? hp[b] : 0u) + hcol[b * kPitch];
   }
+}
+
+// In-kernel consumer with every stream cut into 64 W segments of S draws, one
+// per lane of the W wavefronts that share the stream (W = 1: four streams per
+// workgroup; otherwise a stream per workgroup).  Lane j starts from the
+// stream's state advanced j S draws: one application per set bit of j of the
+// map of S 2^k steps (a multiplier, an affine map, or for XOR128 the object's
+// matrix T^(S 2^k), S a power of two), so no jump data is prepared.  Sums and
+// counts are whole numbers, so they add up to those of one pass whatever the
+// cut.
+//
+// One lane per stream (k_lane_fused) runs ceil(n / 64) wavefronts, 64 of them
+// at 4096 streams, one dependent step after the other; here every SIMD has
+// work from about 1024 / W streams on, and the bound is VALU issue (RANECU:
+// 20 instructions per draw).  4096 streams x 2^20 draws of RANECU: 46.0 ms
+// before, 2.06 ms now (2.1e12 draws/s); 2^30 draws of GGL 0.27 ms.
+//
+// The histogram has 32 columns of 64 bins: the LDS takes a wavefront in halves
+// of 32 lanes, so lanes l and l + 32 share a column without a bank conflict,
+// and at 8.4 KB per wavefront four wavefronts run per SIMD (64 columns: two).
+constexpr int kHistPitch = 33;  // words per bin: 32 columns and one of padding for the final sums
+constexpr int kSplitT = 16;     // draws per unrolled chunk
+constexpr int kMaxSplitBits = 10;
+
+struct SplitMaps {
+  uint64_t a[kMaxSplitBits], c[kMaxSplitBits];  // the map of S 2^k steps
+  const uint32_t* mat;                          // XOR128: T^(S 2^k) at mat + 512 k
+};
+
+template <class G, int W>
+__global__ __launch_bounds__(W == 16 ? 1024 : 256) void k_split_fused(uint32_t* __restrict__ state, uint64_t n,
+                                                                      uint32_t draws, uint32_t S, SplitMaps maps,
+                                                                      uint64_t* __restrict__ sum,
+                                                                      uint32_t* __restrict__ hist, int accumulate) {
+  constexpr int NH = W == 1 ? 4 : 1;  // histograms per workgroup
+  constexpr int kBits = W == 1 ? 6 : W == 4 ? 8 : 10;
+  __shared__ uint32_t hist_all[NH][64 * kHistPitch];
+  __shared__ uint64_t part[W];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t si = W == 1 ? (uint64_t)blockIdx.x * 4u + wave : (uint64_t)blockIdx.x;
+  const bool live = si < n;
+  uint32_t* h = hist_all[W == 1 ? wave : 0];
+  const uint32_t j = W == 1 ? (uint32_t)lane : threadIdx.x;
+  for (uint32_t i = j; i < 64 * kHistPitch; i += 64 * W) h[i] = 0;
+  G g;
+  g.zero();
+  uint32_t cnt = 0;
+  if (live) {
+    uint32_t unused;
+    g.load(state, n, si, unused);
+    cnt = j * S < draws ? min(S, draws - j * S) : 0u;  // j S < 2^30 + 2^20
+    for (int k = 0; k < kBits; ++k) {
+      if constexpr (requires { g.advance_by(maps.mat); }) {
+        if (((j >> k) & 1u) && cnt) g.advance_by(maps.mat + 512 * k);
+      } else {
+        if ((j >> k) & 1u) g.advance(maps.a[k], maps.c[k]);
+      }
+    }
+  }
+  if constexpr (W > 1) __syncthreads();  // the histogram is clear, every wavefront has read the state
+  wave_sync();
+  FusedSink<G::BITS, kHistPitch> sink{0u, h + (lane & 31)};
+  uint64_t total = 0;
+  uint32_t i = 0;
+  for (; i + kSplitT <= cnt; i += kSplitT) {
+    sink.acc = 0;
+    g.template chunk<false>(0u, 0u, 0u, sink);
+    total += sink.acc;
+  }
+  if (i < cnt) {
+    sink.acc = 0;
+    g.template chunk<true>(0u, 0u, cnt - i, sink);
+    total += sink.acc;
+  }
+  if (cnt && j * S + cnt == draws) g.store(state, n, si, 0u, 0u);
+  for (int o = 32; o > 0; o >>= 1) total += (uint64_t)__shfl_xor((unsigned long long)total, o);
+  if constexpr (W > 1) {
+    if (lane == 0) part[wave] = total;
+    __syncthreads();
+    if (wave != 0) return;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) total += part[w];
+  }
+  wave_sync();
+  if (!live) return;
+  uint32_t hb = 0;
+#pragma unroll
+  for (int l = 0; l < 32; ++l) hb += h[lane * kHistPitch + l];
+  if (lane == 0) sum[si] = (accumulate ? sum[si] : 0ull) + total;
+  hist[si * 64u + lane] = (accumulate ? hist[si * 64u + lane] : 0u) + hb;
 }
 
 // Emitter of mt_twist_emit for the fused consumer: the draw's top 24 bits
@@ -122,6 +216,57 @@ hipError_t launch_lane_fused(uint32_t p, uint32_t* st, uint64_t n, uint64_t draw
   return hipGetLastError();
 }
 
+// Wavefronts per stream of a cut run (1, 4 or 16), or 0 for one lane per
+// stream: the least of a time model in draws of one wavefront.  A wavefront
+// pays 40 to start and to add up and `jump` per bit of its segment's number,
+// and its lanes one per draw; 2048 wavefronts run in the time of one.  With
+// one lane per stream a SIMD has at most two wavefronts to hide the dependent
+// steps, at twice the time per draw.  Both sides at 65536 streams x 1024
+// draws, where the model puts them closest: GGL 93 us uncut, 68 us cut;
+// XOR128, whose jumps cost six matrix products, stays uncut at 91 us.
+int split_width(uint64_t n, uint64_t draws, double jump, bool pow2) {
+  auto rounds = [](double waves) { return std::max(1.0, waves / 2048.0); };
+  double best = 2.0 * (double)draws * std::ceil(rounds((double)((n + 63) / 64))) + 40.0;
+  int width = 0;
+  for (int W : {1, 4, 16}) {
+    const int bits = W == 1 ? 6 : W == 4 ? 8 : 10;
+    uint64_t S = (draws + 64ull * W - 1) / (64ull * W);
+    if (pow2) S = std::bit_ceil(S);
+    const double t = rounds((double)n * W) * (40.0 + jump * bits + (double)S);
+    if (t < best) {
+      best = t;
+      width = W;
+    }
+  }
+  return width;
+}
+
+// G: the kind's 16-draw generator; L: its one-lane-per-stream generator
+template <class G, class L>
+hipError_t launch_split_fused(uint32_t* st, uint64_t n, uint64_t draws, uint64_t* sum, uint32_t* hist, bool acc,
+                              hipStream_t s) {
+  // a matrix product of XOR128 costs about 100 of its draws, a multiplication one
+  constexpr bool kXor = requires(G g) { g.advance_by(st); };
+  const int W = split_width(n, draws, kXor ? 100.0 : 1.0, kXor);
+  if (W == 0) return launch_lane_fused<L>(0u, st, n, draws, sum, hist, acc, s);
+  uint64_t S = (draws + 64ull * W - 1) / (64ull * W);
+  SplitMaps maps{};
+  if constexpr (kXor) {
+    S = std::bit_ceil(S);
+    maps.mat = object_tables(XOR128, st, n) + 512 * std::countr_zero(S);  // log2(S) + 9 < 32: S 64 W < 2^31
+  } else {
+    for (int k = 0; k < kMaxSplitBits; ++k) G::q_map(S << k, maps.a[k], maps.c[k]);
+  }
+  const dim3 grid((unsigned)(W == 1 ? (n + 3) / 4 : n));
+  const uint32_t d = (uint32_t)draws, seg = (uint32_t)S;
+  if (W == 1)
+    hipLaunchKernelGGL((k_split_fused<G, 1>), grid, dim3(256), 0, s, st, n, d, seg, maps, sum, hist, acc ? 1 : 0);
+  else if (W == 4)
+    hipLaunchKernelGGL((k_split_fused<G, 4>), grid, dim3(256), 0, s, st, n, d, seg, maps, sum, hist, acc ? 1 : 0);
+  else
+    hipLaunchKernelGGL((k_split_fused<G, 16>), grid, dim3(1024), 0, s, st, n, d, seg, maps, sum, hist, acc ? 1 : 0);
+  return hipGetLastError();
+}
 
 }  // namespace
 
@@ -129,19 +274,19 @@ hipError_t launch_fused(int kind, uint32_t p, uint32_t* st, uint64_t n, uint64_t
                         uint32_t* hist, bool acc, hipStream_t s) {
   switch (kind) {
     case GGL:
-      return launch_lane_fused<Ggl<>>(p, st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Ggl<kSplitT>, Ggl<>>(st, n, draws, sum, hist, acc, s);
     case XOR128:
-      return launch_lane_fused<Xor128<>>(p, st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Xor128<kSplitT>, Xor128<>>(st, n, draws, sum, hist, acc, s);
     case RANECU:
-      return launch_lane_fused<Ranecu<>>(p, st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Ranecu<kSplitT>, Ranecu<>>(st, n, draws, sum, hist, acc, s);
     case RANMAR:
       return launch_lane_fused<Ranmar<>>(p, st, n, draws, sum, hist, acc, s);
     case RANLUX:
       return launch_lane_fused<Ranlux<>>(p, st, n, draws, sum, hist, acc, s);
     case DRAND48:
-      return launch_lane_fused<Drand48<>>(p, st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Drand48<kSplitT>, Drand48<>>(st, n, draws, sum, hist, acc, s);
     case RANNYU:
-      return launch_lane_fused<Rannyu<>>(p, st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Rannyu<kSplitT>, Rannyu<>>(st, n, draws, sum, hist, acc, s);
     case MT19937: {
       const dim3 grid((unsigned)((n + 3) / 4)), block(256);
       hipLaunchKernelGGL(k_mt_fused, grid, block, 0, s, st, n, (uint32_t)draws, sum, hist, acc ? 1 : 0);

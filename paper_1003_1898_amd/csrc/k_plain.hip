@@ -125,32 +125,6 @@ __global__ __launch_bounds__(256) void k_mt_generate(uint32_t* __restrict__ stat
 // from the last (the affine map of 253 steps for the 48-bit LCGs), so every
 // position still costs one multiplication.
 
-constexpr uint64_t cpowmod(uint64_t a, uint64_t e, uint64_t m) {
-  uint64_t r = 1 % m;
-  a %= m;
-  while (e) {
-    if (e & 1) r = r * a % m;
-    a = a * a % m;
-    e >>= 1;
-  }
-  return r;
-}
-
-struct Affine48 {
-  uint64_t a, c;
-};
-// J steps of X -> a X + c mod 2^48 as one affine map
-constexpr Affine48 caffine_pow(uint64_t a, uint64_t c, uint64_t J) {
-  constexpr uint64_t M = (1ull << 48) - 1;
-  Affine48 r{1, 0}, b{a & M, c & M};
-  while (J) {
-    if (J & 1) r = Affine48{(b.a * r.a) & M, (b.a * r.c + b.c) & M};
-    b = Affine48{(b.a * b.a) & M, (b.a * b.c + b.c) & M};
-    J >>= 1;
-  }
-  return r;
-}
-
 constexpr uint32_t kLeapQuad = 4, kLeapBlock = 64 * kLeapQuad;
 
 // a^(4 l + 1) mod m for the 64 lanes: each lane's first position in one multiplication

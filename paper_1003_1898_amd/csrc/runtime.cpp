@@ -201,31 +201,9 @@ PRNG_API int prng_seed_words(int kind, uint64_t master, uint64_t n_streams, uint
   return PRNG_OK;
 }
 
-// Behind the state region: the seed tuples read by the initialisation kernel
-// and, for the kinds whose plain generation cuts streams into jumped segments
-// (RANLUX, XOR128), the snapshot the segments jump from (the seed area is free
-// again once the object exists); then the object's jump tables, written once
-// by prng_create: for RANLUX the 25 block-completion multipliers and the
-// block-jump table of its luxury, for XOR128 the powers T^(2^k).
 namespace {
-bool splits(int kind) { return kind == RANLUX || kind == XOR128; }
-size_t scratch_bytes(int kind, uint64_t n) {
-  size_t b = n * kSeedWords[kind] * 8ull;
-  if (splits(kind)) b = std::max<size_t>(b, state_region_bytes(kind, n));
-  return align256(b);
-}
-size_t table_bytes(int kind) {
-  if (kind == RANLUX) return align256((size_t)(kRanluxAuxWords + kLuxDigitWords) * 4);
-  if (kind == XOR128) return align256((size_t)kXorPow2Words * 4);
-  return 0;
-}
-uint32_t* snapshot_area(const prng_gen* g) {
-  return reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(g->d_state) + state_region_bytes(g->kind, g->n));
-}
-const uint32_t* object_tables(const prng_gen* g) {
-  return reinterpret_cast<const uint32_t*>(reinterpret_cast<char*>(g->d_state) + state_region_bytes(g->kind, g->n) +
-                                           scratch_bytes(g->kind, g->n));
-}
+uint32_t* snapshot_area(const prng_gen* g) { return prng::snapshot_area(g->kind, g->d_state, g->n); }
+const uint32_t* object_tables(const prng_gen* g) { return prng::object_tables(g->kind, g->d_state, g->n); }
 const uint32_t* lux_aux(const prng_gen* g) { return object_tables(g); }
 const uint32_t* lux_digits(const prng_gen* g) { return object_tables(g) + kRanluxAuxWords; }
 }  // namespace
