@@ -56,6 +56,7 @@ namespace prng {
 namespace {
 
 constexpr int kPitch = 65;       // fused histogram: words per bin row (64 lanes + 1 pad word)
+constexpr int kHistPitch = 33;   // cut consumers: words per bin row (32 columns, each of two lanes, + 1 pad word)
 constexpr int kPairPitch = 130;  // stage: words per pair row (64 lanes x 2 draws + 2 pad words)
 
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
@@ -658,6 +659,74 @@ struct Ranmar {
   }
 };
 
+// RANMAR with one stream on a wavefront instead of on a lane.  Putting the
+// recurrence into its own Y_{n-33} gives
+//   Y_n = Y_{n-97} - Y_{n-130} + Y_{n-66}  (mod 2^24),
+// whose shortest lag exceeds 64, so the 64 lanes take 64 consecutive positions
+// per step from a window of 130.  The window sits in an LDS ring of 512 words
+// (position v at word v mod 512); a step is three reads, two additions and a
+// write, at addresses that are the lane's plus a constant, but for the two
+// reads that wrap inside a step.  Values are kept modulo 2^32 and cut to 24
+// bits where they leave the ring.  Steps come in the order S = 0 .. 7, 0, ...
+// of the ring's 64-word pieces.
+struct RanmarWave {
+  static constexpr uint32_t D = Ranmar<>::D, M = Ranmar<>::M, MASK = Ranmar<>::MASK;
+  static constexpr int kRing = 512;
+  uint32_t* ring;
+  int lane;
+  uint32_t w2, w33;  // (lane - 2) mod 512, (lane - 33) mod 512
+  __device__ RanmarWave(uint32_t* r, int l)
+      : ring(r), lane(l), w2((uint32_t)(l - 2) & 511u), w33((uint32_t)(l - 33) & 511u) {}
+  // Positions -97 .. -1 from the stream's state (word m is position m - 97),
+  // then -130 .. -98 by the recurrence backwards: Y_v = Y_{v+97} + Y_{v+64}.
+  // Returns the state's C.
+  __device__ uint32_t load(const uint32_t* st, uint64_t sn, uint64_t si) {
+    const uint32_t a = st[(uint64_t)lane * sn + si];
+    const uint32_t b = lane < 34 ? st[(uint64_t)(64 + lane) * sn + si] : 0u;
+    ring[415 + lane] = a;
+    if (lane < 33) ring[479 + lane] = b;
+    wave_sync();
+    extend_back();
+    return rdlane(b, 33);  // word 97
+  }
+  __device__ void extend_back() {
+    if (lane < 33) ring[382 + lane] = ring[479 + lane] + ring[446 + lane];
+    wave_sync();
+  }
+  // the 64 positions of ring piece S
+  template <int S>
+  __device__ __forceinline__ uint32_t step() {
+    const uint32_t a = S == 1 ? ring[w33] : ring[(64 * S + 415) % 512 + lane];
+    const uint32_t b = S == 2 ? ring[w2] : ring[(64 * S + 382) % 512 + lane];
+    const uint32_t c = S == 1 ? ring[w2] : ring[(64 * S + 446) % 512 + lane];
+    const uint32_t y = a - b + c;
+    ring[64 * S + lane] = y;
+    wave_sync();
+    return y;
+  }
+  template <int H>
+  __device__ __forceinline__ void half() {  // 256 positions
+    step<4 * H>();
+    step<4 * H + 1>();
+    step<4 * H + 2>();
+    step<4 * H + 3>();
+  }
+  // state after `draws` positions; c: the C to go with it
+  __device__ void store(uint32_t* st, uint64_t sn, uint64_t si, uint32_t draws, uint32_t c) const {
+    for (uint32_t m = (uint32_t)lane; m < 97u; m += 64u) st[m * sn + si] = ring[(draws + m + 415u) & 511u] & MASK;
+    if (lane == 0) st[97 * sn + si] = c;
+  }
+  // c - off mod M (both below M)
+  static __device__ __forceinline__ uint32_t c_back(uint32_t c, uint32_t off) {
+    const uint32_t t = c - off;
+    return min(t, t + M);
+  }
+  // C of position v (0 = the next draw) of a stream whose state holds c; v < 512
+  static __device__ __forceinline__ uint32_t c_at(uint32_t c, uint32_t v) { return c_back(c, ((v + 1u) * D) % M); }
+  // off for c_back over q positions
+  static constexpr uint32_t c_off(uint64_t q) { return (uint32_t)(q * D % M); }
+};
+
 // RANLUX (Appendix A.4.5-A.4.6): SWB X_n = X_{n-10} - X_{n-24} - c mod 2^24
 // (borrow c = 1 when negative); after 24 kept values the next p - 24 are
 // discarded.  Register ring R[24]: the slot of step j is j mod 24.  A chunk
@@ -954,6 +1023,44 @@ __device__ __forceinline__ v2u convert_pair(v2u d) {
     o.y = (uint32_t)(b >> 32);
   }
   return o;
+}
+
+template <class L, int DT>
+__device__ __forceinline__ float quad_f32(uint32_t u) {
+  if constexpr (DT == F32P)
+    return L::paper_f32(u);
+  else
+    return to_f32<L::BITS>(u);
+}
+
+// Stores the four draws of positions v .. v+3 (v a multiple of 4): one
+// 16-byte store when all are valid and `vec` (the row is 16-byte aligned),
+// element by element otherwise.  fp64: elements v/2 and v/2 + 1.
+template <class L, int DT>
+__device__ __forceinline__ void quad_emit(uint64_t row, uint32_t v, const uint32_t* u, uint32_t draws, bool vec) {
+  if constexpr (DT == F64) {
+    const double d0 = to_f64<L::BITS>(u[0], u[1]), d1 = to_f64<L::BITS>(u[2], u[3]);
+    const uint64_t p = row + 4ull * v;
+    if (vec && v + 4u <= draws) {
+      const uint64_t b0 = (uint64_t)__double_as_longlong(d0), b1 = (uint64_t)__double_as_longlong(d1);
+      put<v4u, L::kNtOut>(p, v4u{(uint32_t)b0, (uint32_t)(b0 >> 32), (uint32_t)b1, (uint32_t)(b1 >> 32)});
+    } else {  // draws is even: pairs are whole
+      if (v + 2u <= draws) put<double, L::kNtOut>(p, d0);
+      if (v + 4u <= draws) put<double, L::kNtOut>(p + 8u, d1);
+    }
+  } else {
+    uint32_t o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = DT == U32 ? u[j] : __float_as_uint(quad_f32<L, DT>(u[j]));
+    const uint64_t p = row + 4ull * v;
+    if (vec && v + 4u <= draws) {
+      put<v4u, L::kNtOut>(p, v4u{o[0], o[1], o[2], o[3]});
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (v + (uint32_t)j < draws) put<uint32_t, L::kNtOut>(p + 4ull * j, o[j]);
+    }
+  }
 }
 
 // Non-temporal row stores for generators that ask for them (G::kNtOut).

@@ -186,6 +186,14 @@ hipError_t launch_ranlux_variant(int where, uint32_t p, uint32_t* state, uint64_
 // object's tables behind it.
 hipError_t launch_fused(int kind, uint32_t p, uint32_t* state, uint64_t n, uint64_t draws, uint64_t* sum,
                         uint32_t* hist, bool accumulate, hipStream_t s);
+// RANMAR with one stream per wavefront: plain rows, interleaved rows (n a
+// multiple of four) and the in-kernel consumer.
+hipError_t launch_ranmar(int dtype, uint32_t* state, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
+                         uint64_t elem_off, hipStream_t s);
+hipError_t launch_ranmar_packed(int dtype, uint32_t* state, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
+                                uint64_t elem_off, hipStream_t s);
+hipError_t launch_ranmar_fused(uint32_t* state, uint64_t n, uint64_t draws, uint64_t* sum, uint32_t* hist,
+                               bool accumulate, hipStream_t s);
 // Start of a table run: zero n_counters task counters and copy the n
 // snapshot rows, in one kernel.
 hipError_t launch_table_prepare(uint32_t* counters, int n_counters, const SnapRow* rows, uint32_t n,

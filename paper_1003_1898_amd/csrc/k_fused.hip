@@ -71,7 +71,6 @@ __global__ __launch_bounds__(256) void k_lane_fused(uint32_t* __restrict__ state
 // The histogram has 32 columns of 64 bins: the LDS takes a wavefront in halves
 // of 32 lanes, so lanes l and l + 32 share a column without a bank conflict,
 // and at 8.4 KB per wavefront four wavefronts run per SIMD (64 columns: two).
-constexpr int kHistPitch = 33;  // words per bin: 32 columns and one of padding for the final sums
 constexpr int kSplitT = 16;     // draws per unrolled chunk
 constexpr int kMaxSplitBits = 10;
 
@@ -280,7 +279,7 @@ hipError_t launch_fused(int kind, uint32_t p, uint32_t* st, uint64_t n, uint64_t
     case RANECU:
       return launch_split_fused<Ranecu<kSplitT>, Ranecu<>>(st, n, draws, sum, hist, acc, s);
     case RANMAR:
-      return launch_lane_fused<Ranmar<>>(p, st, n, draws, sum, hist, acc, s);
+      return launch_ranmar_fused(st, n, draws, sum, hist, acc, s);
     case RANLUX:
       return launch_lane_fused<Ranlux<>>(p, st, n, draws, sum, hist, acc, s);
     case DRAND48:

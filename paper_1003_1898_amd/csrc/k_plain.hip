@@ -278,44 +278,6 @@ struct LeapLcg48 {
 };
 
 template <class L, int DT>
-__device__ __forceinline__ float leap_f32(uint32_t u) {
-  if constexpr (DT == F32P)
-    return L::paper_f32(u);
-  else
-    return to_f32<L::BITS>(u);
-}
-
-// Stores the four draws of positions v .. v+3 (v a multiple of 4): one
-// 16-byte store when all are valid and `vec` (the row is 16-byte aligned),
-// element by element otherwise.  fp64: elements v/2 and v/2 + 1.
-template <class L, int DT>
-__device__ __forceinline__ void leap_emit(uint64_t row, uint32_t v, const uint32_t* u, uint32_t draws, bool vec) {
-  if constexpr (DT == F64) {
-    const double d0 = to_f64<L::BITS>(u[0], u[1]), d1 = to_f64<L::BITS>(u[2], u[3]);
-    const uint64_t p = row + 4ull * v;
-    if (vec && v + 4u <= draws) {
-      const uint64_t b0 = (uint64_t)__double_as_longlong(d0), b1 = (uint64_t)__double_as_longlong(d1);
-      put<v4u, L::kNtOut>(p, v4u{(uint32_t)b0, (uint32_t)(b0 >> 32), (uint32_t)b1, (uint32_t)(b1 >> 32)});
-    } else {  // draws is even: pairs are whole
-      if (v + 2u <= draws) put<double, L::kNtOut>(p, d0);
-      if (v + 4u <= draws) put<double, L::kNtOut>(p + 8u, d1);
-    }
-  } else {
-    uint32_t o[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = DT == U32 ? u[j] : __float_as_uint(leap_f32<L, DT>(u[j]));
-    const uint64_t p = row + 4ull * v;
-    if (vec && v + 4u <= draws) {
-      put<v4u, L::kNtOut>(p, v4u{o[0], o[1], o[2], o[3]});
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (v + (uint32_t)j < draws) put<uint32_t, L::kNtOut>(p + 4ull * j, o[j]);
-    }
-  }
-}
-
-template <class L, int DT>
 __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ state, uint64_t n, uint32_t draws,
                                                        void* __restrict__ out, uint64_t row_elems, uint64_t elem_off) {
   const int lane = threadIdx.x & 63;
@@ -335,7 +297,7 @@ __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ st
 #pragma unroll 2
   for (; k + 1u < full; ++k) {
     g.quad(u);
-    leap_emit<L, DT>(row, k * kLeapBlock + kLeapQuad * (uint32_t)lane, u, draws, vec);
+    quad_emit<L, DT>(row, k * kLeapBlock + kLeapQuad * (uint32_t)lane, u, draws, vec);
     g.leap();
   }
   // the last one or two blocks: a lane leaps only if it has a later position;
@@ -346,7 +308,7 @@ __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ st
     if (v < draws) {
       L h = g;  // quad() moves the state to the quad's last position
       h.quad(u);
-      leap_emit<L, DT>(row, v, u, draws, vec);
+      quad_emit<L, DT>(row, v, u, draws, vec);
       if (v + kLeapBlock < draws) {
         h.leap();
         g = h;
@@ -394,7 +356,7 @@ __global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ st
     // blocks whose next block is still inside the quarter: fill, then leap
     for (; v + kLeapBlock + (kLeapBlock - kLeapQuad * (uint32_t)lane) <= end; v += kLeapBlock) {
       h.quad(u);
-      leap_emit<L, DT>(row, v, u, end, vec);
+      quad_emit<L, DT>(row, v, u, end, vec);
       h.leap();
     }
     // the remaining one or two blocks: leap only towards a later position
@@ -402,7 +364,7 @@ __global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ st
       if (v < end) {
         L q = h;
         q.quad(u);
-        leap_emit<L, DT>(row, v, u, end, vec);
+        quad_emit<L, DT>(row, v, u, end, vec);
         if (v + kLeapBlock < end) {
           q.leap();
           h = q;
@@ -525,6 +487,16 @@ hipError_t launch_lane_gen(int dtype, uint32_t p, uint32_t* st, uint64_t n, uint
   return hipGetLastError();
 }
 
+// RANMAR runs one stream per lane when the lanes keep at least three quarters
+// of the 1024 SIMDs busy (one wavefront each; its window takes most of the
+// registers), one per wavefront otherwise.  A lane's time does not fall with
+// the stream count: f32, per lane and per wavefront, 65536 x 4096 182 and 260
+// us (the lanes' rows are stored in longer runs), 65536 x 1024 57 and 67 us,
+// 16384 x 4096 155 and 48 us, 4096 x 1000 55 and 8.3 us.
+bool lanes_fill(uint64_t n) {
+  const uint64_t waves = (n + 63) / 64, rounds = (waves + 1023) / 1024;
+  return 4 * waves >= 3 * 1024 * rounds;
+}
 
 }  // namespace
 
@@ -538,7 +510,8 @@ hipError_t launch_generate(int kind, uint32_t p, uint32_t* st, uint64_t n, uint6
     case RANECU:
       return launch_leap<LeapRanecu>(dtype, st, n, draws, out, row_elems, off, s);
     case RANMAR:
-      return launch_lane_gen<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      if (lanes_fill(n)) return launch_lane_gen<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      return launch_ranmar(dtype, st, n, draws, out, row_elems, off, s);
     case DRAND48:
       return launch_leap<LeapLcg48<25214903917ull, 11u>>(dtype, st, n, draws, out, row_elems, off, s);
     case RANNYU:
@@ -605,7 +578,8 @@ hipError_t launch_generate_packed(int kind, uint32_t p, uint32_t* st, uint64_t n
     case RANECU:
       return launch_lane_pack<Ranecu<>>(dtype, p, st, n, draws, out, row_elems, off, s);
     case RANMAR:
-      return launch_lane_pack<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      if (lanes_fill(n)) return launch_lane_pack<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      return launch_ranmar_packed(dtype, st, n, draws, out, row_elems, off, s);
     case RANLUX:
       return launch_lane_pack<Ranlux<96>>(dtype, p, st, n, draws, out, row_elems, off, s);
     case DRAND48:
