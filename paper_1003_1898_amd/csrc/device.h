@@ -70,9 +70,12 @@ typedef __attribute__((address_space(1))) double gf64;
 // plain launches, that pays where much ALU and LDS work sits between the
 // stores (MT19937: 7-10% faster; RANECU's leapfrog kernel: 3%) and costs 1-5%
 // in the store-bound lane kernels, so each kernel picks.
+// A dword-aligned address is enough for a vector store to global memory (an LDS
+// access needs its full alignment).
 template <class T, bool NT = false>
 __device__ __forceinline__ void put(uint64_t addr, T v) {
-  auto* p = reinterpret_cast<__attribute__((address_space(1))) T*>(addr);
+  typedef T __attribute__((aligned(4))) A;
+  auto* p = reinterpret_cast<__attribute__((address_space(1))) A*>(addr);
   if constexpr (NT)
     __builtin_nontemporal_store(v, p);
   else
@@ -1034,31 +1037,36 @@ __device__ __forceinline__ float quad_f32(uint32_t u) {
 }
 
 // Stores the four draws of positions v .. v+3 (v a multiple of 4): one
-// 16-byte store when all are valid and `vec` (the row is 16-byte aligned),
-// element by element otherwise.  fp64: elements v/2 and v/2 + 1.
-template <class L, int DT>
-__device__ __forceinline__ void quad_emit(uint64_t row, uint32_t v, const uint32_t* u, uint32_t draws, bool vec) {
+// 16-byte store when all are valid and the row allows it, element by element
+// otherwise.  fp64: elements v/2 and v/2 + 1.  QUADS says that the row is
+// 16-byte aligned; rows that are only dword-aligned take the same store,
+// always cached (non-temporal stores of lines that two instructions share cost
+// three times as much).  Such rows went element by element before: RANECU
+// 10007 x 1537 f32 50 -> 17 us, GGL 22 -> 12 us.
+template <class L, int DT, bool QUADS>
+__device__ __forceinline__ void quad_emit(uint64_t row, uint32_t v, const uint32_t* u, uint32_t draws) {
+  constexpr bool NT = QUADS && L::kNtOut;
+  const uint64_t p = row + 4ull * v;
+  const bool whole = v + 4u <= draws && (QUADS || (row & 3u) == 0u);
   if constexpr (DT == F64) {
     const double d0 = to_f64<L::BITS>(u[0], u[1]), d1 = to_f64<L::BITS>(u[2], u[3]);
-    const uint64_t p = row + 4ull * v;
-    if (vec && v + 4u <= draws) {
+    if (whole) {
       const uint64_t b0 = (uint64_t)__double_as_longlong(d0), b1 = (uint64_t)__double_as_longlong(d1);
-      put<v4u, L::kNtOut>(p, v4u{(uint32_t)b0, (uint32_t)(b0 >> 32), (uint32_t)b1, (uint32_t)(b1 >> 32)});
+      put<v4u, NT>(p, v4u{(uint32_t)b0, (uint32_t)(b0 >> 32), (uint32_t)b1, (uint32_t)(b1 >> 32)});
     } else {  // draws is even: pairs are whole
-      if (v + 2u <= draws) put<double, L::kNtOut>(p, d0);
-      if (v + 4u <= draws) put<double, L::kNtOut>(p + 8u, d1);
+      if (v + 2u <= draws) put<double, NT>(p, d0);
+      if (v + 4u <= draws) put<double, NT>(p + 8u, d1);
     }
   } else {
     uint32_t o[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) o[j] = DT == U32 ? u[j] : __float_as_uint(quad_f32<L, DT>(u[j]));
-    const uint64_t p = row + 4ull * v;
-    if (vec && v + 4u <= draws) {
-      put<v4u, L::kNtOut>(p, v4u{o[0], o[1], o[2], o[3]});
+    if (whole) {
+      put<v4u, NT>(p, v4u{o[0], o[1], o[2], o[3]});
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        if (v + (uint32_t)j < draws) put<uint32_t, L::kNtOut>(p + 4ull * j, o[j]);
+        if (v + (uint32_t)j < draws) put<uint32_t, NT>(p + 4ull * j, o[j]);
     }
   }
 }
@@ -1075,7 +1083,7 @@ constexpr int store_aux() {
     return 0;
 }
 
-template <class G, int DT, int T, class SV>
+template <class G, int DT, int T, int AUX, class SV>
 __device__ __forceinline__ void emit_full_plain(const SV& st, int lane, __amdgpu_buffer_rsrc_t rs,
                                                 uint32_t row_bytes) {
   using RS = RowSplit<T>;
@@ -1085,7 +1093,7 @@ __device__ __forceinline__ void emit_full_plain(const SV& st, int lane, __amdgpu
 #pragma unroll
   for (int r = 0; r < 64; r += RS::RPI) {
     const v2u d = st.pair(P, r + h);
-    __builtin_amdgcn_raw_buffer_store_b64(convert_pair<G, DT>(d), rs, voff, (uint32_t)r * row_bytes, store_aux<G>());
+    __builtin_amdgcn_raw_buffer_store_b64(convert_pair<G, DT>(d), rs, voff, (uint32_t)r * row_bytes, AUX);
   }
 }
 
@@ -1132,7 +1140,7 @@ __device__ __forceinline__ void emit_general(const SV& st, int lane, uint32_t lo
 // Chunk whose 64 rows are arbitrary output rows and each emits only the
 // positions of its own range [ebeg, vend) inside the chunk (the first and last
 // chunks of uneven segments): stores as in emit_full_rows, with a pair cut by
-// its row's range, or a row not 8-byte aligned, written as 4-byte elements.
+// its row's range, or a row not dword-aligned, written as 4-byte elements.
 // fp64 needs every row's pairs to start at even positions (ebeg even).
 template <class G, int DT, int T, class SV>
 __device__ __forceinline__ void emit_partial_rows(const SV& st, int lane, uint32_t lo, uint64_t q, uint32_t ebeg,
@@ -1160,7 +1168,7 @@ __device__ __forceinline__ void emit_partial_rows(const SV& st, int lane, uint32
       if (in0 && in1) put<double>(rq + 4ull * v0, to_f64<G::BITS>(d.x, d.y));
     } else {
       const v2u o = convert_pair<G, DT>(d);
-      if (in0 && in1 && ((rq & 7u) == 0u)) {
+      if (in0 && in1 && ((rq & 3u) == 0u)) {
         put<v2u>(rq + 4ull * v0, o);
       } else {
         if (in0) put<uint32_t>(rq + 4ull * v0, o.x);
@@ -1233,16 +1241,18 @@ __device__ __forceinline__ void lane_loop(G& g, uint32_t* stage, int lane, uint3
   const uint32_t maxE = wave_max(has ? vend : 0u);
   const uint32_t ming = wave_min(has ? gbeg : 0xFFFFFFFFu);
   const uint32_t nlive = uni((uint32_t)__popcll(__ballot(has)));
-  const uint32_t nalign = uni((uint32_t)__popcll(__ballot(has && (q & 7u) == 0u)));
+  const uint32_t nalign = uni((uint32_t)__popcll(__ballot(has && (q & (DT == F64 ? 7u : 3u)) == 0u)));
   // fp64 pairs of every row start at even positions (so a chunk's pairs are the rows' pairs)
   const bool even_pairs = DT != F64 || uni((uint32_t)__popcll(__ballot(has && ((ebeg & 1u) || (q & 7u))))) == 0u;
-  // every row live and 8-byte aligned at even positions: unchecked 8-byte stores
+  // every row live and dword-aligned (fp64: 8-byte aligned at even positions): unchecked 8-byte stores
   const bool even = nlive == 64u && nalign == 64u;
   // the rows must also sit exactly row_bytes apart (streams at different
   // positions of their blocks may share a segment-local start)
   const uint64_t q0 = rdlane64(q, 0);
   const uint32_t nstride = uni((uint32_t)__popcll(__ballot(q == q0 + (uint64_t)lane * row_bytes)));
   plain = plain && even && nstride == 64u && minb == maxb && 63ull * row_bytes + 4ull * T < 0x7FFFFFFFull;
+  // rows of whole 8-byte steps, which a generator may store non-temporally
+  const bool lines = ((q0 | row_bytes) & 7u) == 0u;
   // row 0's element at the common first position (lane 0 is live when plain)
   uint8_t* const wave_base = reinterpret_cast<uint8_t*>(q0 + 4ull * minb);
   // interleaved rows: every lane live, a common start, and each group's row
@@ -1270,7 +1280,10 @@ __device__ __forceinline__ void lane_loop(G& g, uint32_t* stage, int lane, uint3
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             wave_base + 4ull * (uint64_t)(lo - minb), (short)0, (int)(63u * (uint32_t)row_bytes + 4u * T),
             0x00020000);
-        emit_full_plain<G, DT, T>(st, lane, rs, (uint32_t)row_bytes);
+        if (store_aux<G>() == 0 || lines)
+          emit_full_plain<G, DT, T, store_aux<G>()>(st, lane, rs, (uint32_t)row_bytes);
+        else
+          emit_full_plain<G, DT, T, 0>(st, lane, rs, (uint32_t)row_bytes);
       } else if (even) {
         emit_full_rows<G, DT, T>(st, lane, lo, q);
       } else if (even_pairs) {

@@ -277,7 +277,7 @@ struct LeapLcg48 {
   }
 };
 
-template <class L, int DT>
+template <class L, int DT, bool QUADS>
 __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ state, uint64_t n, uint32_t draws,
                                                        void* __restrict__ out, uint64_t row_elems, uint64_t elem_off) {
   const int lane = threadIdx.x & 63;
@@ -289,7 +289,6 @@ __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ st
   constexpr uint64_t es = DT == F64 ? 8 : 4;
   // position v's element at byte row + 4 v (an fp64 element per pair of draws)
   const uint64_t row = reinterpret_cast<uint64_t>(out) + (s * row_elems + elem_off) * es;
-  const bool vec = (row & 15u) == 0u;
   // blocks k with 256 (k + 2) <= draws: every lane fills its four positions and leaps
   const uint32_t full = draws / kLeapBlock;
   uint32_t k = 0;
@@ -297,7 +296,7 @@ __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ st
 #pragma unroll 2
   for (; k + 1u < full; ++k) {
     g.quad(u);
-    quad_emit<L, DT>(row, k * kLeapBlock + kLeapQuad * (uint32_t)lane, u, draws, vec);
+    quad_emit<L, DT, QUADS>(row, k * kLeapBlock + kLeapQuad * (uint32_t)lane, u, draws);
     g.leap();
   }
   // the last one or two blocks: a lane leaps only if it has a later position;
@@ -308,7 +307,7 @@ __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ st
     if (v < draws) {
       L h = g;  // quad() moves the state to the quad's last position
       h.quad(u);
-      quad_emit<L, DT>(row, v, u, draws, vec);
+      quad_emit<L, DT, QUADS>(row, v, u, draws);
       if (v + kLeapBlock < draws) {
         h.leap();
         g = h;
@@ -327,7 +326,7 @@ __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ st
 // store order measured 4-5% faster than one wavefront per row.  Every
 // wavefront reads the four states before the barrier; the wavefront of a
 // row's last position writes its new state after it.
-template <class L, int DT>
+template <class L, int DT, bool QUADS>
 __global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ state, uint64_t n, uint32_t draws,
                                                        uint32_t Q, uint64_t j0, uint64_t j1, void* __restrict__ out,
                                                        uint64_t row_elems, uint64_t elem_off) {
@@ -350,13 +349,12 @@ __global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ st
     h.advance_q(j0, j1, w);  // X of position w Q
     h.start(lane);           // X of position w Q + 4 l
     const uint64_t row = reinterpret_cast<uint64_t>(out) + (s * row_elems + elem_off) * es;
-    const bool vec = (row & 15u) == 0u;
     uint32_t u[4];
     uint32_t v = beg + kLeapQuad * (uint32_t)lane;
     // blocks whose next block is still inside the quarter: fill, then leap
     for (; v + kLeapBlock + (kLeapBlock - kLeapQuad * (uint32_t)lane) <= end; v += kLeapBlock) {
       h.quad(u);
-      quad_emit<L, DT>(row, v, u, end, vec);
+      quad_emit<L, DT, QUADS>(row, v, u, end);
       h.leap();
     }
     // the remaining one or two blocks: leap only towards a later position
@@ -364,7 +362,7 @@ __global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ st
       if (v < end) {
         L q = h;
         q.quad(u);
-        quad_emit<L, DT>(row, v, u, end, vec);
+        quad_emit<L, DT, QUADS>(row, v, u, end);
         if (v + kLeapBlock < end) {
           q.leap();
           h = q;
@@ -376,28 +374,55 @@ __global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ st
   }
 }
 
-template <class L>
-hipError_t launch_leap_quarters(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
-                                uint64_t off, hipStream_t s) {
-  const uint64_t Q = ((draws + 3) / 4 + kLeapBlock - 1) / kLeapBlock * kLeapBlock;
-  uint64_t j0 = 0, j1 = 0;
-  L::q_map(Q, j0, j1);
+template <class L, bool QUADS>
+hipError_t launch_leap_rows(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
+                            uint64_t off, hipStream_t s) {
   const dim3 grid((unsigned)((n + 3) / 4)), block(256);
-  const uint32_t d = (uint32_t)draws, q = (uint32_t)Q;
+  const uint32_t d = (uint32_t)draws;
+  // rows of at least four blocks per wavefront go by quarters
+  if (draws >= 16 * kLeapBlock) {
+    const uint64_t Q = ((draws + 3) / 4 + kLeapBlock - 1) / kLeapBlock * kLeapBlock;
+    const uint32_t q = (uint32_t)Q;
+    uint64_t j0 = 0, j1 = 0;
+    L::q_map(Q, j0, j1);
+    switch (dtype) {
+      case U32:
+        hipLaunchKernelGGL((k_leap_quarters<L, U32, QUADS>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems,
+                           off);
+        break;
+      case F32:
+        hipLaunchKernelGGL((k_leap_quarters<L, F32, QUADS>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems,
+                           off);
+        break;
+      case F64:
+        hipLaunchKernelGGL((k_leap_quarters<L, F64, QUADS>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems,
+                           off);
+        break;
+      case F32P:
+        if constexpr (requires { L::paper_f32(0u); }) {
+          hipLaunchKernelGGL((k_leap_quarters<L, F32P, QUADS>), grid, block, 0, s, st, n, d, q, j0, j1, out,
+                             row_elems, off);
+          break;
+        }
+        return hipErrorInvalidValue;
+      default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   switch (dtype) {
     case U32:
-      hipLaunchKernelGGL((k_leap_quarters<L, U32>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems, off);
+      hipLaunchKernelGGL((k_leap_generate<L, U32, QUADS>), grid, block, 0, s, st, n, d, out, row_elems, off);
       break;
     case F32:
-      hipLaunchKernelGGL((k_leap_quarters<L, F32>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems, off);
+      hipLaunchKernelGGL((k_leap_generate<L, F32, QUADS>), grid, block, 0, s, st, n, d, out, row_elems, off);
       break;
     case F64:
-      hipLaunchKernelGGL((k_leap_quarters<L, F64>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems, off);
+      hipLaunchKernelGGL((k_leap_generate<L, F64, QUADS>), grid, block, 0, s, st, n, d, out, row_elems, off);
       break;
     case F32P:
       if constexpr (requires { L::paper_f32(0u); }) {
-        hipLaunchKernelGGL((k_leap_quarters<L, F32P>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems,
-                           off);
+        hipLaunchKernelGGL((k_leap_generate<L, F32P, QUADS>), grid, block, 0, s, st, n, d, out, row_elems, off);
         break;
       }
       return hipErrorInvalidValue;
@@ -407,33 +432,14 @@ hipError_t launch_leap_quarters(int dtype, uint32_t* st, uint64_t n, uint64_t dr
   return hipGetLastError();
 }
 
+// every row 16-byte aligned, or rows at any alignment
 template <class L>
 hipError_t launch_leap(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
                        uint64_t off, hipStream_t s) {
-  // rows of at least four blocks per wavefront go by quarters
-  if (draws >= 16 * kLeapBlock) return launch_leap_quarters<L>(dtype, st, n, draws, out, row_elems, off, s);
-  const dim3 grid((unsigned)((n + 3) / 4)), block(256);
-  const uint32_t d = (uint32_t)draws;
-  switch (dtype) {
-    case U32:
-      hipLaunchKernelGGL((k_leap_generate<L, U32>), grid, block, 0, s, st, n, d, out, row_elems, off);
-      break;
-    case F32:
-      hipLaunchKernelGGL((k_leap_generate<L, F32>), grid, block, 0, s, st, n, d, out, row_elems, off);
-      break;
-    case F64:
-      hipLaunchKernelGGL((k_leap_generate<L, F64>), grid, block, 0, s, st, n, d, out, row_elems, off);
-      break;
-    case F32P:
-      if constexpr (requires { L::paper_f32(0u); }) {
-        hipLaunchKernelGGL((k_leap_generate<L, F32P>), grid, block, 0, s, st, n, d, out, row_elems, off);
-        break;
-      }
-      return hipErrorInvalidValue;
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  const uint64_t es = elem_bytes(dtype);
+  if (((reinterpret_cast<uint64_t>(out) + off * es) | (n > 1 ? row_elems * es : 0)) % 16 == 0)
+    return launch_leap_rows<L, true>(dtype, st, n, draws, out, row_elems, off, s);
+  return launch_leap_rows<L, false>(dtype, st, n, draws, out, row_elems, off, s);
 }
 
 template <class G>

@@ -39,7 +39,6 @@ struct StateTile {
 template <int DT>
 __device__ __forceinline__ void ranmar_row(RanmarWave& w, uint32_t c0, uint32_t draws, uint64_t row) {
   const int lane = w.lane;
-  const bool vec = (row & 15u) == 0u;
   uint32_t c = RanmarWave::c_at(c0, 4u * (uint32_t)lane);  // C of position v
   uint32_t v = 4u * (uint32_t)lane;
   auto emit = [&](int h) {
@@ -48,7 +47,7 @@ __device__ __forceinline__ void ranmar_row(RanmarWave& w, uint32_t c0, uint32_t 
                            (y.y - RanmarWave::c_back(c, RanmarWave::c_off(1))) & RanmarWave::MASK,
                            (y.z - RanmarWave::c_back(c, RanmarWave::c_off(2))) & RanmarWave::MASK,
                            (y.w - RanmarWave::c_back(c, RanmarWave::c_off(3))) & RanmarWave::MASK};
-    if (v < draws) quad_emit<RanmarOut, DT>(row, v, u, draws, vec);
+    if (v < draws) quad_emit<RanmarOut, DT, false>(row, v, u, draws);
     c = RanmarWave::c_back(c, RanmarWave::c_off(256));
     v += 256u;
   };
