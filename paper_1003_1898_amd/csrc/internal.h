@@ -165,6 +165,9 @@ constexpr uint32_t kLuxSplitMax = 64;
 hipError_t launch_lux_fused_split(uint32_t p, uint32_t* st, const uint32_t* snap, uint64_t n, uint64_t draws,
                                   uint32_t S, uint32_t K, const uint32_t* digits, const uint32_t* aux, uint64_t* sum,
                                   uint32_t* hist, bool acc, hipStream_t s);
+// From this many streams on, one lane per stream keeps the SIMDs busy by
+// itself and XOR128's segments are few and long (128-draw chunks).
+constexpr uint64_t kXorLanes = 32768;
 // XOR128 plain generation with every stream cut into K >= 2 segments of S
 // positions (a multiple of 128), 256 streams per block and segment, so that
 // several wavefronts per SIMD share the stores.  snap: copy of the state

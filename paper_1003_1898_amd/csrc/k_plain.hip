@@ -47,13 +47,15 @@ __global__ __launch_bounds__(256) void k_lane_generate(uint32_t* __restrict__ st
 // the snapshot `snap` taken before the launch, segment j > 0 jumped j S
 // positions ahead; the last segment writes the final state.  XOR128's draws
 // carry no position structure, so segments run in the stream's own
-// coordinates; S is even, so fp64 pairs never straddle a boundary.
-template <int DT>
+// coordinates; S is even, so fp64 pairs never straddle a boundary.  64-draw
+// chunks put two workgroups on a CU; long launches of many streams, bound by
+// their stores, take 128-draw chunks.
+template <int DT, int TT>
 __global__ __launch_bounds__(256) void k_xor128_split(uint32_t* __restrict__ state, const uint32_t* __restrict__ snap,
                                                       uint64_t n, uint32_t draws, uint32_t S, uint32_t K,
                                                       const uint32_t* __restrict__ pow2, void* __restrict__ out,
                                                       uint64_t row_elems, uint64_t elem_off) {
-  using G = Xor128<>;
+  using G = Xor128<TT>;
   constexpr uint32_t T = G::T;
   __shared__ __attribute__((aligned(16))) uint32_t stage_all[4][stage_words<T>()];
   const int lane = threadIdx.x & 63;
@@ -549,29 +551,42 @@ hipError_t launch_generate(int kind, uint32_t p, uint32_t* st, uint64_t n, uint6
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_xor128_split(uint32_t* st, const uint32_t* snap, uint64_t n, uint64_t draws, int dtype, uint32_t S,
-                               uint32_t K, const uint32_t* pow2, void* out, uint64_t row_elems, uint64_t off,
-                               hipStream_t s) {
+namespace {
+template <int TT>
+hipError_t launch_xor128_chunks(uint32_t* st, const uint32_t* snap, uint64_t n, uint64_t draws, int dtype, uint32_t S,
+                                uint32_t K, const uint32_t* pow2, void* out, uint64_t row_elems, uint64_t off,
+                                hipStream_t s) {
   const dim3 grid((unsigned)((n + 255) / 256 * K)), block(256);
   const uint32_t d = (uint32_t)draws;
   switch (dtype) {
     case U32:
-      hipLaunchKernelGGL((k_xor128_split<U32>), grid, block, 0, s, st, snap, n, d, S, K, pow2, out, row_elems, off);
+      hipLaunchKernelGGL((k_xor128_split<U32, TT>), grid, block, 0, s, st, snap, n, d, S, K, pow2, out, row_elems,
+                         off);
       break;
     case F32:
-      hipLaunchKernelGGL((k_xor128_split<F32>), grid, block, 0, s, st, snap, n, d, S, K, pow2, out, row_elems, off);
+      hipLaunchKernelGGL((k_xor128_split<F32, TT>), grid, block, 0, s, st, snap, n, d, S, K, pow2, out, row_elems,
+                         off);
       break;
     case F64:
-      hipLaunchKernelGGL((k_xor128_split<F64>), grid, block, 0, s, st, snap, n, d, S, K, pow2, out, row_elems, off);
+      hipLaunchKernelGGL((k_xor128_split<F64, TT>), grid, block, 0, s, st, snap, n, d, S, K, pow2, out, row_elems,
+                         off);
       break;
     case F32P:
-      hipLaunchKernelGGL((k_xor128_split<F32P>), grid, block, 0, s, st, snap, n, d, S, K, pow2, out, row_elems,
+      hipLaunchKernelGGL((k_xor128_split<F32P, TT>), grid, block, 0, s, st, snap, n, d, S, K, pow2, out, row_elems,
                          off);
       break;
     default:
       return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_xor128_split(uint32_t* st, const uint32_t* snap, uint64_t n, uint64_t draws, int dtype, uint32_t S,
+                               uint32_t K, const uint32_t* pow2, void* out, uint64_t row_elems, uint64_t off,
+                               hipStream_t s) {
+  if (n >= kXorLanes) return launch_xor128_chunks<128>(st, snap, n, draws, dtype, S, K, pow2, out, row_elems, off, s);
+  return launch_xor128_chunks<64>(st, snap, n, draws, dtype, S, K, pow2, out, row_elems, off, s);
 }
 
 hipError_t launch_generate_packed(int kind, uint32_t p, uint32_t* st, uint64_t n, uint64_t draws, int dtype,

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <bit>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -275,13 +276,17 @@ namespace {
 // prng_generate with the pre-launch snapshot of RANLUX and XOR128 (the kinds
 // whose streams are cut into jumped segments) at `snap_area` (the object's
 // scratch area, or the device's static scratch for prng_generate_noalloc).
+// The static scratch is shared by every call on the GPU: `shared` calls use it
+// only where they are long enough to gain much by it (short calls on several
+// HIP streams at once stay independent).
 int generate_with(prng_gen* g, uint64_t count, int dtype, void* d_out, size_t out_bytes, void* stream,
-                  uint32_t* snap_area);
+                  uint32_t* snap_area, bool shared);
 }  // namespace
 
 PRNG_API int prng_generate(prng_gen* g, uint64_t count, int dtype, void* d_out, size_t out_bytes, void* stream) {
   if (!g) return fail(PRNG_EINVAL, "g is NULL");
-  return generate_with(g, count, dtype, d_out, out_bytes, stream, splits(g->kind) ? snapshot_area(g) : nullptr);
+  return generate_with(g, count, dtype, d_out, out_bytes, stream, splits(g->kind) ? snapshot_area(g) : nullptr,
+                       false);
 }
 
 PRNG_API int prng_generate_noalloc(prng_gen* g, uint64_t count, int dtype, void* d_out, size_t out_bytes,
@@ -299,12 +304,12 @@ PRNG_API int prng_generate_noalloc(prng_gen* g, uint64_t count, int dtype, void*
     HIP_TRY(static_scratch(g->device, &p));
     snap = static_cast<uint32_t*>(p);
   }
-  return generate_with(g, count, dtype, d_out, out_bytes, stream, snap);
+  return generate_with(g, count, dtype, d_out, out_bytes, stream, snap, true);
 }
 
 namespace {
 int generate_with(prng_gen* g, uint64_t count, int dtype, void* d_out, size_t out_bytes, void* stream,
-                  uint32_t* snap_area) {
+                  uint32_t* snap_area, bool shared) {
   if (dtype < U32 || dtype > F32P) return fail(PRNG_EINVAL, "unknown dtype %d", dtype);
   if (dtype == F32P && (g->kind == DRAND48 || g->kind == RANNYU))
     return fail(PRNG_EUNSUPPORTED, "no paper single-precision rule for generator kind %d", g->kind);
@@ -344,23 +349,32 @@ int generate_with(prng_gen* g, uint64_t count, int dtype, void* d_out, size_t ou
       continue;
     }
     if (g->kind == XOR128) {
-      // Cut each stream into K segments (jumped starts, each at least 2048
-      // draws) so that about 4096 wavefronts are launched: at small stream
-      // counts they fill SIMDs that one lane per stream would leave idle.
-      // A workgroup's 128-draw stage takes 134 KB of LDS, so one runs per
-      // CU and at 65536 streams the segments run one after another.
+      // Cut each stream into K segments with jumped starts.  From kXorLanes
+      // streams on, one lane per stream comes near to filling the SIMDs and
+      // segments of at least 2048 draws, about 4096 wavefronts in all, run one
+      // workgroup per CU (a 128-draw stage takes 134 KB of LDS).  Below, about
+      // 2048 wavefronts in segments of a power of two from 128 draws on: a
+      // jump costs a matrix product (2 us) per set bit of its distance, and
+      // the power of two leaves only those of the segment's number.  f64 4096
+      // x 2000: 127 us uncut, 34 us in 32 segments; f32 10007 x 1537 88 and 30
+      // us, 65536 x 1024 44 us uncut and 47 us in two.
       const uint64_t d = c * per;
       const uint64_t waves = (g->n + 63) / 64;
-      uint64_t K = std::min<uint64_t>({8, (4096 + waves - 1) / waves, std::max<uint64_t>(1, d / 2048)});
+      uint64_t S;
+      if (g->n < kXorLanes) {
+        const uint64_t want = 2048 / waves;
+        S = shared && d < 4096 ? d : std::max<uint64_t>(128, std::bit_ceil((d + want - 1) / want));
+      } else {
+        const uint64_t K =
+            std::min<uint64_t>({8, (4096 + waves - 1) / waves, std::max<uint64_t>(1, d / 2048)});
+        S = ((d + K - 1) / K + 127) / 128 * 128;
+      }
+      const uint64_t K = (d + S - 1) / S;  // (K - 1) S < d: no segment is empty
       if (K > 1) {
-        const uint64_t S = ((d + K - 1) / K + 127) / 128 * 128;
-        K = (d + S - 1) / S;  // (K - 1) S < d: no segment is empty
-        if (K > 1) {
-          HIP_TRY(hipMemcpyAsync(snap_area, g->d_state, state_region_bytes(XOR128, g->n), hipMemcpyDeviceToDevice, s));
-          HIP_TRY(launch_xor128_split(g->d_state, snap_area, g->n, d, dtype, (uint32_t)S, (uint32_t)K,
-                                      object_tables(g), d_out, count, off, s));
-          continue;
-        }
+        HIP_TRY(hipMemcpyAsync(snap_area, g->d_state, state_region_bytes(XOR128, g->n), hipMemcpyDeviceToDevice, s));
+        HIP_TRY(launch_xor128_split(g->d_state, snap_area, g->n, d, dtype, (uint32_t)S, (uint32_t)K,
+                                    object_tables(g), d_out, count, off, s));
+        continue;
       }
     }
     HIP_TRY(launch_generate(g->kind, g->p, g->d_state, g->n, c * per, dtype, d_out, count, off, s));
