@@ -158,10 +158,14 @@ template <uint32_t C>
 __device__ __forceinline__ uint32_t mulmod_2p31(uint32_t x, uint32_t a) {
   constexpr uint32_t M = 0x80000000u - C;
   const uint64_t p = (uint64_t)x * a;
-  uint64_t r = (p >> 31) * C + (p & 0x7FFFFFFFull);
-  r = (r >> 31) * C + (r & 0x7FFFFFFFull);
-  const uint32_t t = (uint32_t)r;
-  return t >= M ? t - M : t;
+  uint32_t t = (uint32_t)p & 0x7FFFFFFFu;
+  if constexpr (C == 1) {  // one fold: both parts are below 2^31
+    t += (uint32_t)(p >> 31);
+  } else {
+    const uint64_t r = (uint64_t)(uint32_t)(p >> 31) * C + t;
+    t = (uint32_t)(r >> 31) * C + ((uint32_t)r & 0x7FFFFFFFu);
+  }
+  return min(t, t - M);
 }
 
 // a^e mod m and the affine map of J steps of a 48-bit LCG, for jump constants
@@ -308,6 +312,7 @@ struct Ggl {
     j1 = 0;
   }
   __device__ void advance(uint64_t j0, uint64_t) { x = mulmod_2p31<1u>(x, (uint32_t)j0); }
+  __device__ uint32_t draw() const { return x; }  // of the step that led here
   template <bool PRED, class S>
   __device__ __forceinline__ void chunk(uint32_t lo, uint32_t vbeg, uint32_t vend, S& sink) {
 #pragma unroll
@@ -443,6 +448,10 @@ struct Ranecu {
     s1 = mulmod_2p31<85u>(s1, (uint32_t)j0);
     s2 = mulmod_2p31<249u>(s2, (uint32_t)j1);
   }
+  __device__ uint32_t draw() const {
+    const int32_t z = (int32_t)s1 - (int32_t)s2;
+    return (uint32_t)(z + ((z <= 0) ? 2147483562 : 0));
+  }
   template <bool PRED, class S>
   __device__ __forceinline__ void chunk(uint32_t lo, uint32_t vbeg, uint32_t vend, S& sink) {
 #pragma unroll
@@ -499,6 +508,7 @@ struct Lcg48 {
     x0 = (uint32_t)y;
     x1 = (uint32_t)(y >> 32) & 0xFFFFu;
   }
+  __device__ uint32_t draw() const { return (x1 << 16) | (x0 >> 16); }
   template <bool PRED, class S>
   __device__ __forceinline__ void chunk(uint32_t lo, uint32_t vbeg, uint32_t vend, S& sink) {
 #pragma unroll
@@ -518,6 +528,14 @@ template <int TT = 128>
 using Drand48 = Lcg48<TT, 25214903917ull, 11u>;
 template <int TT = 128>
 using Rannyu = Lcg48<TT, 31167285ull, 0u>;
+
+// Maps of S 2^k steps, as kernel arguments: a lane of up to 1024 advances a
+// stream by its number times S with one application per set bit.
+constexpr int kMaxSplitBits = 10;
+struct SplitMaps {
+  uint64_t a[kMaxSplitBits], c[kMaxSplitBits];
+  const uint32_t* mat;  // XOR128: T^(S 2^k) at mat + 512 k
+};
 
 // RANMAR (Appendix A.4.4): Y_n = Y_{n-97} - Y_{n-33} mod 2^24,
 // C_n = C_{n-1} - 7654321 mod (2^24 - 3), X_n = Y_n - C_n mod 2^24.

@@ -72,13 +72,6 @@ __global__ __launch_bounds__(256) void k_lane_fused(uint32_t* __restrict__ state
 // of 32 lanes, so lanes l and l + 32 share a column without a bank conflict,
 // and at 8.4 KB per wavefront four wavefronts run per SIMD (64 columns: two).
 constexpr int kSplitT = 16;     // draws per unrolled chunk
-constexpr int kMaxSplitBits = 10;
-
-struct SplitMaps {
-  uint64_t a[kMaxSplitBits], c[kMaxSplitBits];  // the map of S 2^k steps
-  const uint32_t* mat;                          // XOR128: T^(S 2^k) at mat + 512 k
-};
-
 template <class G, int W>
 __global__ __launch_bounds__(W == 16 ? 1024 : 256) void k_split_fused(uint32_t* __restrict__ state, uint64_t n,
                                                                       uint32_t draws, uint32_t S, SplitMaps maps,

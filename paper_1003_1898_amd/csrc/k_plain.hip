@@ -1,5 +1,5 @@
 // Plain bulk generation: leapfrog kernels (GGL, RANECU, DRAND48, RANNYU), lane-per-stream kernels
-// (XOR128, RANMAR; and every lane kind for four-way interleaved output) and MT19937.
+// (XOR128, RANMAR; and, for four-way interleaved output, RANLUX) and MT19937.
 #include <array>
 
 #include "device.h"
@@ -444,6 +444,97 @@ hipError_t launch_leap(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void
   return launch_leap_rows<L, false>(dtype, st, n, draws, out, row_elems, off, s);
 }
 
+// Interleaved rows of the multiplicative and affine generators: W wavefronts
+// on the four streams of a row, lane t of them at positions t, t + 64 W, ...,
+// leaping by the map of 64 W steps, so that a store instruction writes 1 KB of
+// the row and no LDS is needed.  Lane t's first position is the state advanced
+// t + 1 steps: maps.a[0] is the map of one step, and one application per set
+// bit of t follows.  Bound by the stores (GGL 16384 x 4096 f32, one lane per
+// stream through an LDS transpose on 256 wavefronts: 117 us before, 51 us now).
+template <class G, int DT, int W>
+__global__ __launch_bounds__(W == 16 ? 1024 : 256) void k_leap_pack4(uint32_t* __restrict__ state, uint64_t n,
+                                                                     uint32_t draws, SplitMaps maps, uint64_t leap_a,
+                                                                     uint64_t leap_c, void* __restrict__ out,
+                                                                     uint64_t row_elems, uint64_t elem_off) {
+  constexpr int kBits = W == 1 ? 6 : W == 4 ? 8 : 10;
+  const uint64_t row = W == 1 ? (uint64_t)blockIdx.x * 4u + (threadIdx.x >> 6) : (uint64_t)blockIdx.x;
+  const uint32_t t = W == 1 ? threadIdx.x & 63u : threadIdx.x;
+  const bool live = 4u * row < n;  // n is a multiple of four
+  G g[4];
+  if (live) {
+    uint32_t unused;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) g[k].load(state, n, 4u * row + k, unused);
+  }
+  if constexpr (W > 1) __syncthreads();  // every wavefront has read the states
+  if (!live || t >= draws) return;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) g[k].advance(maps.a[0], maps.c[0]);
+  for (int b = 0; b < kBits; ++b) {
+    if ((t >> b) & 1u) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) g[k].advance(maps.a[b], maps.c[b]);
+    }
+  }
+  uint64_t at = reinterpret_cast<uint64_t>(out) + (row * row_elems + elem_off + t) * 16ull;
+  for (uint32_t v = t;; v += 64u * W) {
+    uint32_t o[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = DT == U32 ? g[k].draw() : __float_as_uint(cvt32<G, DT>(g[k].draw()));
+    put<v4u>(at, v4u{o[0], o[1], o[2], o[3]});
+    if (draws - v <= 64u * W) {  // the lane's last position; the row's last one gives the new states
+      if (v == draws - 1u) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) g[k].store(state, n, 4u * row + k, 0u, 0u);
+      }
+      return;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) g[k].advance(leap_a, leap_c);
+    at += 1024ull * W;
+  }
+}
+
+template <class G, int W>
+hipError_t launch_leap_pack_w(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
+                              uint64_t off, hipStream_t s) {
+  const uint64_t rows = n / 4;
+  const dim3 grid((unsigned)(W == 1 ? (rows + 3) / 4 : rows)), block(W == 16 ? 1024 : 256);
+  const uint32_t d = (uint32_t)draws;
+  SplitMaps maps{};
+  for (int k = 0; k < kMaxSplitBits; ++k) G::q_map(1ull << k, maps.a[k], maps.c[k]);
+  uint64_t la = 0, lc = 0;
+  G::q_map(64ull * W, la, lc);
+  switch (dtype) {
+    case U32:
+      hipLaunchKernelGGL((k_leap_pack4<G, U32, W>), grid, block, 0, s, st, n, d, maps, la, lc, out, row_elems, off);
+      break;
+    case F32:
+      hipLaunchKernelGGL((k_leap_pack4<G, F32, W>), grid, block, 0, s, st, n, d, maps, la, lc, out, row_elems, off);
+      break;
+    case F32P:
+      if constexpr (requires { G::paper_f32(0u); }) {
+        hipLaunchKernelGGL((k_leap_pack4<G, F32P, W>), grid, block, 0, s, st, n, d, maps, la, lc, out, row_elems,
+                           off);
+        break;
+      }
+      return hipErrorInvalidValue;
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// wavefronts per row of four streams: about 4096 in all, none without a position
+template <class G>
+hipError_t launch_leap_pack(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
+                            uint64_t off, hipStream_t s) {
+  const uint64_t want = std::min((4096 + n / 4 - 1) / (n / 4), (draws + 63) / 64);
+  if (want >= 16) return launch_leap_pack_w<G, 16>(dtype, st, n, draws, out, row_elems, off, s);
+  if (want >= 4) return launch_leap_pack_w<G, 4>(dtype, st, n, draws, out, row_elems, off, s);
+  return launch_leap_pack_w<G, 1>(dtype, st, n, draws, out, row_elems, off, s);
+}
+
 template <class G>
 hipError_t launch_lane_pack(int dtype, uint32_t p, uint32_t* st, uint64_t n, uint64_t draws, void* out,
                             uint64_t row_elems, uint64_t off, hipStream_t s) {
@@ -593,20 +684,20 @@ hipError_t launch_generate_packed(int kind, uint32_t p, uint32_t* st, uint64_t n
                                   void* out, uint64_t row_elems, uint64_t off, hipStream_t s) {
   switch (kind) {
     case GGL:
-      return launch_lane_pack<Ggl<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      return launch_leap_pack<Ggl<>>(dtype, st, n, draws, out, row_elems, off, s);
     case XOR128:
       return launch_lane_pack<Xor128<>>(dtype, p, st, n, draws, out, row_elems, off, s);
     case RANECU:
-      return launch_lane_pack<Ranecu<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      return launch_leap_pack<Ranecu<>>(dtype, st, n, draws, out, row_elems, off, s);
     case RANMAR:
       if (lanes_fill(n)) return launch_lane_pack<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
       return launch_ranmar_packed(dtype, st, n, draws, out, row_elems, off, s);
     case RANLUX:
       return launch_lane_pack<Ranlux<96>>(dtype, p, st, n, draws, out, row_elems, off, s);
     case DRAND48:
-      return launch_lane_pack<Drand48<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      return launch_leap_pack<Drand48<>>(dtype, st, n, draws, out, row_elems, off, s);
     case RANNYU:
-      return launch_lane_pack<Rannyu<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      return launch_leap_pack<Rannyu<>>(dtype, st, n, draws, out, row_elems, off, s);
   }
   return hipErrorInvalidValue;
 }
