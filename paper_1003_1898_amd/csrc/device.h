@@ -116,6 +116,11 @@ __device__ __forceinline__ uint32_t rdlane(uint32_t v, int l) {
 __device__ __forceinline__ uint64_t rdlane64(uint64_t v, int l) {
   return ((uint64_t)rdlane((uint32_t)(v >> 32), l) << 32) | rdlane((uint32_t)v, l);
 }
+template <class P>
+__device__ __forceinline__ P* uni_ptr(P* p) {  // the wavefront's common address, for scalar loads
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return reinterpret_cast<P*>(((uint64_t)uni((uint32_t)(a >> 32)) << 32) | uni((uint32_t)a));
+}
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
   for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o));
   return uni(v);
@@ -352,7 +357,7 @@ struct Xor128 {
   __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd, const uint32_t*,
                                   uint32_t*) {
     uint32_t s[4] = {st[si], st[sn + si], st[2 * sn + si], st[3 * sn + si]};
-    matvec(s, jd);
+    matvec<8>(s, jd);
     x = s[0];
     y = s[1];
     z = s[2];
@@ -360,14 +365,16 @@ struct Xor128 {
     return 0;
   }
   // one product with a 128x128 GF(2) matrix in the row layout of load_jumped:
-  // every state bit costs its mask and one xor-and per word; a word's 32 rows
-  // are unrolled so that the scalar loads of many rows are in flight (eight at
-  // a time: 4096 x 2000 f64 38 us instead of 34)
+  // every state bit costs its mask and one xor-and per word.  U rows of a word
+  // are unrolled: 32 where the matrix is the wavefront's, so that the scalar
+  // loads of many rows are in flight (eight at a time: 4096 x 2000 f64 38 us
+  // instead of 34), 8 where each lane has its own
+  template <int U>
   __device__ static void matvec(uint32_t* s, const uint32_t* __restrict__ m) {
     uint32_t o[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-#pragma unroll
+#pragma unroll U
       for (int i = 0; i < 32; ++i) {
         const uint32_t mask = 0u - ((s[q] >> i) & 1u);
         const v4u row = *reinterpret_cast<const v4u*>(m + 128 * q + 4 * i);
@@ -382,7 +389,7 @@ struct Xor128 {
   }
   __device__ void advance_by(const uint32_t* __restrict__ m) {
     uint32_t s[4] = {x, y, z, w};
-    matvec(s, m);
+    matvec<32>(s, m);
     x = s[0];
     y = s[1];
     z = s[2];
@@ -393,7 +400,7 @@ struct Xor128 {
   __device__ void load_jumped_pow2(const uint32_t* st, uint64_t sn, uint64_t si, uint32_t E, const uint32_t* pow2) {
     uint32_t s[4] = {st[si], st[sn + si], st[2 * sn + si], st[3 * sn + si]};
     for (int k = 0; k < kXorPow2; ++k)
-      if ((E >> k) & 1u) matvec(s, pow2 + 512 * k);
+      if ((E >> k) & 1u) matvec<32>(s, pow2 + 512 * k);
     x = s[0];
     y = s[1];
     z = s[2];
@@ -579,37 +586,6 @@ struct Ranmar {
     si_ = si;
     stored_ = st == nullptr;
   }
-  // Window J steps ahead.  With x^k standing for Y_{n-97+k}, the recurrence
-  // reads x^97 = 1 - x^64, and Y_{n-97+J+t} is the dot product of the window
-  // with the coefficients of x^{J+t} mod (x^97 + x^64 - 1).  jd[0..96] holds
-  // x^J mod that polynomial; each further t multiplies by x (shift, fold the
-  // top coefficient into x^0 and x^64).  New window values go through the
-  // lane's LDS column `col` (stride 64 words) because t is a loop index.
-  // jd[97] = J D mod M rewinds C.
-  __device__ uint32_t load_jumped(uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd, const uint32_t*,
-                                  uint32_t* col) {
-    uint32_t unused;
-    load(st, sn, si, unused);
-    uint32_t c[97];
-#pragma unroll
-    for (int i = 0; i < 97; ++i) c[i] = jd[i];
-    for (int t = 0; t < 97; ++t) {
-      uint32_t acc[4] = {0u, 0u, 0u, 0u};  // four independent sums
-#pragma unroll
-      for (int i = 0; i < 97; ++i) acc[i & 3] += __umul24(c[i], R[i]);
-      col[t * 64] = (acc[0] + acc[1] + acc[2] + acc[3]) & MASK;
-      const uint32_t top = c[96];
-#pragma unroll
-      for (int i = 96; i > 0; --i) c[i] = c[i - 1];
-      c[0] = top;
-      c[64] -= top;
-    }
-#pragma unroll
-    for (int m = 0; m < 97; ++m) R[m] = col[m * 64];
-    const uint32_t r = jd[97];
-    C = C >= r ? C - r : C + (M - r);
-    return 0;
-  }
   __device__ void store(uint32_t* st, uint64_t sn, uint64_t si, uint32_t, uint32_t) {
     if (stored_) return;
 #pragma unroll
@@ -715,6 +691,33 @@ struct RanmarWave {
   __device__ void extend_back() {
     if (lane < 33) ring[382 + lane] = ring[479 + lane] + ring[446 + lane];
     wave_sync();
+  }
+  // The window J steps ahead.  With x^k standing for Y_{n-97+k}, the recurrence
+  // reads x^97 = 1 - x^64, and Y_{n-97+J+t} is the dot product of the
+  // coefficients of x^J mod (x^97 + x^64 - 1), jd[0 .. 96], with the sequence
+  // from value t of the window on, which two steps extend far enough; lane l
+  // takes t = l and l + 64.  jd[97] = J D mod M rewinds C.
+  __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* __restrict__ jd) {
+    const uint32_t c = load(st, sn, si);
+    step<0>();
+    step<1>();
+    uint32_t* lin = ring + 128;  // the sequence of 193 values in a row (positions 128 .. 381 are free)
+    for (uint32_t m = (uint32_t)lane; m < 193u; m += 64u) lin[m] = ring[(415u + m) & 511u];
+    wave_sync();
+    uint32_t a = 0, b = 0;
+    const int hi = lane < 33 ? lane + 64 : lane;  // lanes 33 .. 63 have one value
+#pragma unroll 16
+    for (int i = 0; i < 97; ++i) {
+      const uint32_t k = jd[i];
+      a += __umul24(k, lin[lane + i]);
+      b += __umul24(k, lin[hi + i]);
+    }
+    wave_sync();
+    ring[415 + lane] = a;
+    if (lane < 33) ring[479 + lane] = b;
+    wave_sync();
+    extend_back();
+    return c_back(c, jd[97]);
   }
   // the 64 positions of ring piece S
   template <int S>
@@ -1088,6 +1091,38 @@ __device__ __forceinline__ void quad_emit(uint64_t row, uint32_t v, const uint32
       for (int j = 0; j < 4; ++j)
         if (v + (uint32_t)j < draws) put<uint32_t, NT>(p + 4ull * j, o[j]);
     }
+  }
+}
+
+// `draws` positions of a RANMAR stream by one wavefront, whose ring holds the
+// window of a state with C = c0, to the row at byte address `row`.
+struct RanmarOut {  // quad_emit's generator traits
+  static constexpr int BITS = 24;
+  static constexpr bool kNtOut = false;
+  static __device__ float paper_f32(uint32_t u) { return Ranmar<>::paper_f32(u); }
+};
+
+template <int DT>
+__device__ __forceinline__ void ranmar_row(RanmarWave& w, uint32_t c0, uint32_t draws, uint64_t row) {
+  const int lane = w.lane;
+  uint32_t c = RanmarWave::c_at(c0, 4u * (uint32_t)lane);  // C of position v
+  uint32_t v = 4u * (uint32_t)lane;
+  auto emit = [&](int h) {
+    const v4u y = *reinterpret_cast<const v4u*>(w.ring + 256 * h + 4 * lane);
+    const uint32_t u[4] = {(y.x - c) & RanmarWave::MASK,
+                           (y.y - RanmarWave::c_back(c, RanmarWave::c_off(1))) & RanmarWave::MASK,
+                           (y.z - RanmarWave::c_back(c, RanmarWave::c_off(2))) & RanmarWave::MASK,
+                           (y.w - RanmarWave::c_back(c, RanmarWave::c_off(3))) & RanmarWave::MASK};
+    if (v < draws) quad_emit<RanmarOut, DT, false>(row, v, u, draws);
+    c = RanmarWave::c_back(c, RanmarWave::c_off(256));
+    v += 256u;
+  };
+  for (uint32_t pos = 0; pos < draws; pos += 512u) {
+    w.half<0>();
+    emit(0);
+    if (pos + 256u >= draws) break;
+    w.half<1>();
+    emit(1);
   }
 }
 
@@ -1731,17 +1766,11 @@ __device__ __forceinline__ uint32_t next_task(uint32_t* counter, int lane) {
   return uni((uint32_t)__shfl((int)t, 0));
 }
 
-// Lane-per-stream tasks come in two kernels (classes).  GGL, XOR128, RANECU,
-// DRAND48 and RANNYU take 64-draw chunks (a 16.5 KB LDS stage per
-// wavefront) and RANLUX 96-draw chunks in the three-byte stage (18.7 KB), so
+// Lane-per-stream tasks take 64-draw chunks (a 16.5 KB LDS stage per
+// wavefront), RANLUX's 96-draw chunks in the three-byte stage (18.7 KB), so
 // two blocks share a CU: a second wavefront per SIMD overlaps its work (for
-// RANLUX the borrow chain) with the other's stores.  RANMAR (97-word window
-// plus a chunk of new values in registers, and a 97 x 97 jump) needs most of
-// the register file, one wavefront per SIMD; with the CU to itself it takes
-// 128-draw chunks (a 32.8 KB stage per wavefront), which halves the window
-// moves per draw.
-constexpr int kClassT[kLaneClasses] = {64, 128};
-constexpr int kLuxTableT = 96;
+// RANLUX the borrow chain) with the other's stores.
+constexpr int kTableT = 64, kLuxTableT = 96;
 
 }  // namespace
 }  // namespace prng

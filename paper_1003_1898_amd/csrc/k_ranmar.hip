@@ -5,12 +5,6 @@
 namespace prng {
 namespace {
 
-struct RanmarOut {  // quad_emit's generator traits
-  static constexpr int BITS = 24;
-  static constexpr bool kNtOut = false;
-  static __device__ float paper_f32(uint32_t u) { return Ranmar<>::paper_f32(u); }
-};
-
 // Workgroup index under which each run of Q consecutive ones is on one XCD
 // (workgroups go to the eight XCDs in turn), so that the 128-byte lines of the
 // state rows, 32 streams each, are not fetched by all eight of them.
@@ -35,30 +29,6 @@ struct StateTile {
       if (s0 + i % (4 * R) < n) st[(uint64_t)(i / (4 * R)) * n + s0 + i % (4 * R)] = w[i % (4 * R)][i / (4 * R)];
   }
 };
-
-template <int DT>
-__device__ __forceinline__ void ranmar_row(RanmarWave& w, uint32_t c0, uint32_t draws, uint64_t row) {
-  const int lane = w.lane;
-  uint32_t c = RanmarWave::c_at(c0, 4u * (uint32_t)lane);  // C of position v
-  uint32_t v = 4u * (uint32_t)lane;
-  auto emit = [&](int h) {
-    const v4u y = *reinterpret_cast<const v4u*>(w.ring + 256 * h + 4 * lane);
-    const uint32_t u[4] = {(y.x - c) & RanmarWave::MASK,
-                           (y.y - RanmarWave::c_back(c, RanmarWave::c_off(1))) & RanmarWave::MASK,
-                           (y.z - RanmarWave::c_back(c, RanmarWave::c_off(2))) & RanmarWave::MASK,
-                           (y.w - RanmarWave::c_back(c, RanmarWave::c_off(3))) & RanmarWave::MASK};
-    if (v < draws) quad_emit<RanmarOut, DT, false>(row, v, u, draws);
-    c = RanmarWave::c_back(c, RanmarWave::c_off(256));
-    v += 256u;
-  };
-  for (uint32_t pos = 0; pos < draws; pos += 512u) {
-    w.half<0>();
-    emit(0);
-    if (pos + 256u >= draws) break;
-    w.half<1>();
-    emit(1);
-  }
-}
 
 // R streams per wavefront, one after the other (R = 1: states read and written
 // directly).  Bound by LDS latency at few streams (four dependent steps per

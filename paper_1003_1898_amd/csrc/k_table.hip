@@ -4,19 +4,13 @@
 namespace prng {
 namespace {
 
-template <int CLASS>
 __global__ __launch_bounds__(256) void k_table_lane(const TableTask* __restrict__ tasks, uint32_t ntasks,
                                                     const TableRow* __restrict__ rows,
                                                     const uint32_t* __restrict__ tails, uint32_t* counter,
                                                     const uint32_t* __restrict__ aux) {
-  constexpr int TS = kClassT[CLASS];
-  // RANMAR's jump also passes 97 values per lane through the stage (stride
-  // 64), which its 128-draw stage holds; RANLUX, in class 0, stages its
-  // 24-bit draws of 96-draw chunks in three bytes, which takes a little more
-  // than the 64-draw word stage
-  constexpr int SW = CLASS == 0 ? std::max(stage_words<TS>(), (StageSplit24<kLuxTableT>::kBytes + 3) / 4)
-                     : stage_words<TS>() < 97 * 64 ? 97 * 64
-                                                   : stage_words<TS>();
+  // RANLUX's three-byte stage of 96-draw chunks takes a little more than the
+  // 64-draw word stage
+  constexpr int SW = std::max(stage_words<kTableT>(), (StageSplit24<kLuxTableT>::kBytes + 3) / 4);
   __shared__ __attribute__((aligned(16))) uint32_t stage_all[4][SW];
   const int lane = threadIdx.x & 63;
   uint32_t* stage = stage_all[threadIdx.x >> 6];
@@ -27,25 +21,61 @@ __global__ __launch_bounds__(256) void k_table_lane(const TableTask* __restrict_
   case K * 4 + U32: lane_task<G, U32, SPLIT>(stage, lane, rows, tails, task, p, aux); break; \
   case K * 4 + F32: lane_task<G, F32, SPLIT>(stage, lane, rows, tails, task, p, aux); break; \
   case K * 4 + F64: lane_task<G, F64, SPLIT>(stage, lane, rows, tails, task, p, aux); break;
-    if constexpr (CLASS == 0) {
-      switch (kind * 4 + dt) {
-        PRNG_TASK(GGL, Ggl<64>, false)
-        PRNG_TASK(XOR128, Xor128<64>, false)
-        PRNG_TASK(RANECU, Ranecu<64>, false)
-        PRNG_TASK(DRAND48, Drand48<64>, false)
-        PRNG_TASK(RANNYU, Rannyu<64>, false)
-        PRNG_TASK(RANLUX, Ranlux<kLuxTableT>, true)
-        default:
-          break;
-      }
-    } else {
-      switch (kind * 4 + dt) {
-        PRNG_TASK(RANMAR, Ranmar<kClassT[1]>, false)
-        default:
-          break;
-      }
+    switch (kind * 4 + dt) {
+      PRNG_TASK(GGL, Ggl<kTableT>, false)
+      PRNG_TASK(XOR128, Xor128<kTableT>, false)
+      PRNG_TASK(RANECU, Ranecu<kTableT>, false)
+      PRNG_TASK(DRAND48, Drand48<kTableT>, false)
+      PRNG_TASK(RANNYU, Rannyu<kTableT>, false)
+      PRNG_TASK(RANLUX, Ranlux<kLuxTableT>, true)
+      default:
+        break;
     }
 #undef PRNG_TASK
+    wave_sync();
+  }
+}
+
+// RANMAR tasks, segment by segment: a wavefront pulls one segment of a task's
+// (up to 64) at a time, so that a task's segments spread over the chip, and
+// generates it as the plain kernel does.  The jump costs about as much as 500
+// draws (97 reads and products for 97 window values); one lane per segment,
+// as the other kinds run, it costs 20k operations per lane and the window and
+// its chunk take a SIMD's registers for a single wavefront.
+__global__ __launch_bounds__(256) void k_table_ranmar(const TableTask* __restrict__ tasks, uint32_t ntasks,
+                                                      const TableRow* __restrict__ rows,
+                                                      const uint32_t* __restrict__ tails, uint32_t* counter) {
+  __shared__ __attribute__((aligned(16))) uint32_t ring_all[4][RanmarWave::kRing];
+  const int lane = threadIdx.x & 63;
+  RanmarWave w(ring_all[threadIdx.x >> 6], lane);
+  for (uint32_t u = next_task(counter, lane); u / 64u < ntasks; u = next_task(counter, lane)) {
+    const TableTask& task = tasks[u / 64u];
+    if (u % 64u >= uni(task.nseg)) continue;
+    const uint64_t g = task.g0 + u % 64u;
+    uint32_t r, j;
+    if (task.tail) {
+      r = uni(tails[g]);
+      j = rows[r].nseg - 1u;
+    } else {
+      r = uni(segment_row(rows, task, g));
+      j = (uint32_t)(g - rows[r].first);
+    }
+    const TableRow& rw = *uni_ptr(rows + r);
+    const uint32_t S = rw.seg_len, beg = j * S, last = j + 1u == rw.nseg ? 1u : 0u;
+    const uint32_t draws = (last ? rw.draws : beg + S) - beg;  // S is even: fp64 pairs stay whole
+    const uint32_t c0 = j == 0 ? w.load(rw.state, rw.sn, rw.si)
+                               : w.load_jumped(rw.state, rw.sn, rw.si, uni_ptr(rw.jump + (j - 1u) * rw.jstride));
+    const uint64_t row = reinterpret_cast<uint64_t>(rw.out) + 4ull * beg;
+    const uint32_t dt = uni(task.dtype);
+    if (dt == U32)
+      ranmar_row<U32>(w, c0, draws, row);
+    else if (dt == F32)
+      ranmar_row<F32>(w, c0, draws, row);
+    else
+      ranmar_row<F64>(w, c0, draws, row);
+    if (last)
+      w.store(rw.wstate, rw.wsn, rw.wsi, draws,
+              RanmarWave::c_back(c0, (uint32_t)((uint64_t)draws * RanmarWave::D % RanmarWave::M)));
     wave_sync();
   }
 }
@@ -240,9 +270,9 @@ __global__ void k_table_prepare(uint32_t* counters, int n_counters, const SnapRo
 hipError_t launch_table_lane(int cls, const TableTask* tasks, uint32_t ntasks, const TableRow* rows,
                              const uint32_t* tails, uint32_t* counter, const uint32_t* aux, int grid, hipStream_t s) {
   if (cls == 0)
-    hipLaunchKernelGGL((k_table_lane<0>), dim3(grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter, aux);
-  else
-    hipLaunchKernelGGL((k_table_lane<1>), dim3(grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter, aux);
+    hipLaunchKernelGGL(k_table_lane, dim3(grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter, aux);
+  else  // RANMAR: eight blocks per CU, a wavefront per segment
+    hipLaunchKernelGGL(k_table_ranmar, dim3(8 * grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter);
   return hipGetLastError();
 }
 

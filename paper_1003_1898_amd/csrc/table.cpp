@@ -103,7 +103,8 @@ int prng::make_plan(prng_gen* const* gens, int n_gens, const prng_table_row* row
     if (v == kSegAuto) return automatic;
     return roundup(std::max<uint64_t>(v, lo), align);
   };
-  // RANMAR's jump costs ~20k operations: automatically four lane lengths
+  // RANMAR's segments are a wavefront's, which runs 64 positions at a time:
+  // automatically four lane lengths
   const uint64_t L_lane = resolve(seg.lane, lane_auto, kSegAlign, kSegAlign);
   const uint64_t L_ranmar = resolve(seg.ranmar, 4 * lane_auto, kSegAlign, kSegAlign);
   const uint64_t L_mt = resolve(seg.mt, mt_auto, 1248, 624);
@@ -339,8 +340,8 @@ void drop_graph(prng_table* t) {
 // build the jumped MT19937 windows, then the persistent kernels.  cfg.concurrent
 // 0: all of them one after the other; 1: the lane classes one after the
 // other, MT19937 beside them on a forked stream; 2: MT19937 and every lane
-// class on a stream of its own, so that a class with few tasks (RANMAR, one
-// wavefront per SIMD) leaves the rest of the chip to the others; 3: as 2, but
+// class on a stream of its own, so that a class whose tasks run out leaves its
+// part of the chip to the others; 3: as 2, but
 // the lane classes start before the MT19937 jumps, which run on MT19937's
 // stream (a few 1024-thread blocks with 88 KB of LDS each that otherwise hold
 // the chip alone).  Forked streams join `s` at the end.
@@ -353,8 +354,8 @@ hipError_t prng::enqueue_run(prng_table* t, hipStream_t s) {
   const int mode = used > 1 ? t->cfg.concurrent : 0;
   // Modes 2 and 3: a persistent kernel fills whatever CUs are free, so the one
   // dispatched first holds most of the chip until its list runs dry.  RANMAR's
-  // class (few wavefronts, long tasks) goes first, on `s` itself, where it
-  // does not wait for the fork event; the other kernels fill the rest.
+  // class, the shortest, goes first, on `s` itself, where it does not wait for
+  // the fork event; the others take the room it leaves.
   const int primary = mode >= 2 && t->n_class_tasks[1] ? 1 : 0;
   // kernel k: lane class k < kLaneClasses, MT19937 for k == kLaneClasses;
   // side slot of a lane class other than the primary one (-1: on `s`)
@@ -391,18 +392,11 @@ hipError_t prng::enqueue_run(prng_table* t, hipStream_t s) {
     const int full = kClassFullGrid[c] * t->cfg.lane_grid / 256;
     return std::max(1, std::min<int>(full, (int)((t->n_class_tasks[c] + 3) / 4)));
   };
-  // Modes 2 and 3: the other kernels leave room for the primary class's
-  // blocks (one per CU at most), whatever order the dispatchers start them
-  // in; otherwise persistent blocks that arrived first would keep it waiting
-  // until their lists ran dry.
-  const int reserved = mode >= 2 ? std::min(192, lane_grid_of(primary) * 256 / kClassFullGrid[primary]) : 0;
   auto launch_lane = [&](int c) -> hipError_t {
     const uint32_t n = t->n_class_tasks[c];
     if (!n) return hipSuccess;
-    int g = lane_grid_of(c);
-    if (mode >= 2 && c != primary) g = std::max(1, g * (256 - reserved) / 256);
-    return launch_table_lane(c, t->d_class_tasks[c], n, t->d_rows, t->d_tails, t->d_counters + c, t->d_aux, g,
-                             stream_of(c));
+    return launch_table_lane(c, t->d_class_tasks[c], n, t->d_rows, t->d_tails, t->d_counters + c, t->d_aux,
+                             lane_grid_of(c), stream_of(c));
   };
   // mode 3: the lane classes do not wait for the MT19937 jumps, which run on
   // MT19937's stream; otherwise the jumps come first, over the whole chip
@@ -412,8 +406,7 @@ hipError_t prng::enqueue_run(prng_table* t, hipStream_t s) {
   if (mode != 3 && (e = fork_all()) != hipSuccess) return e;
   if (mode >= 2 && (e = launch_lane(primary)) != hipSuccess) return e;
   if (t->n_mt_tasks) {  // beside the lane kernels (5 KB of LDS per block)
-    int g = std::min<int>(t->cfg.mt_grid, (int)t->n_mt_tasks);  // one task per workgroup
-    if (mode >= 2) g = std::max(1, g * (256 - reserved) / 256);
+    const int g = std::min<int>(t->cfg.mt_grid, (int)t->n_mt_tasks);  // one task per workgroup
     if ((e = launch_table_mt(t->d_mt_tasks, t->n_mt_tasks, t->d_rows, t->d_counters + kLaneClasses, g,
                              stream_of(kLaneClasses))) != hipSuccess)
       return e;
