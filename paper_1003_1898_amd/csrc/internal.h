@@ -204,7 +204,7 @@ hipError_t launch_table_prepare(uint32_t* counters, int n_counters, const SnapRo
 // Lane-per-stream task classes of the stream table and the blocks (of four
 // wavefronts) that fill the chip for each: GGL/XOR128/RANECU/DRAND48/RANNYU
 // and RANLUX (its 96-draw chunks staged in three bytes), two per CU; RANMAR,
-// whose kernel takes a segment per wavefront and eight times these blocks.
+// whose kernel takes a segment per wavefront and sixteen times these blocks.
 constexpr int kLaneClasses = 2;
 constexpr int kClassFullGrid[kLaneClasses] = {512, 256};
 inline int lane_class(int kind) { return kind == RANMAR ? 1 : 0; }

@@ -136,26 +136,58 @@ __global__ __launch_bounds__(256) void k_table_mt(const TableTask* __restrict__ 
 // i of x^J mod the characteristic polynomial (the segment's jump data lists
 // their exponents).  The low 31 bits of word 0 are not part of the state and
 // come out arbitrary; the next twist reads only its top bit.
+//
+// The LDS bounds it: word by word, about 10^4 coefficients read 624 words each
+// (142 us a block).  Coefficients are therefore taken six at a time: the groups
+// i = 6 b of one pattern w of set bits are summed first, S_w[m] = XOR of
+// x_{6b+m}, into B_t = XOR of S_w over the patterns with bit t, and word k is
+// the XOR of B_t[k + t], t = 0 .. 5: some 3800 reads (a group each, padded per
+// pattern) of 630 words.
 constexpr int kMtSeqWords = 624 + 19936;
-constexpr int kJumpThreads = 1024;  // four groups of 256 split the exponents
+constexpr int kJumpThreads = 1024;  // four teams of 256 split each pattern's groups
+constexpr int kJumpQ = 6, kJumpPatterns = 1 << kJumpQ;
+constexpr int kJumpGroups = (19937 + kJumpQ - 1) / kJumpQ;
+constexpr int kJumpSpan = 624 + kJumpQ - 1;      // words a group is read for
+constexpr int kJumpZero = kMtSeqWords + 8;       // zeros, for the padding groups (a last group reads two words past the sequence)
+constexpr int kJumpPitch = kJumpSpan + 3;
+constexpr int kJumpRound = 16;                   // groups per round: four of each team
+constexpr int kJumpList = (kJumpGroups + (kJumpPatterns - 1) * (kJumpRound - 1) + 7) / 8 * 8;
+static_assert(kJumpZero + kJumpPitch < 65536, "list entries are 16 bits");
+static_assert(4 * kJumpQ * kJumpPitch <= kJumpZero, "the teams' sums reuse the sequence");
 
 __global__ __launch_bounds__(kJumpThreads) void k_table_mt_jump(const uint32_t* __restrict__ list, uint32_t n,
                                                                 const TableRow* __restrict__ rows) {
-  __shared__ uint32_t seq[kMtSeqWords];
-  __shared__ uint32_t part[3][624];  // partial windows of groups 1..3
+  __shared__ uint32_t seq[kJumpZero + kJumpPitch];
+  __shared__ uint32_t coef[624 + 1];  // bit i of the polynomial
+  __shared__ __attribute__((aligned(16))) uint16_t groups[kJumpList];
+  __shared__ uint32_t first[kJumpPatterns + 1], cursor[kJumpPatterns];
   const int tid = threadIdx.x;
-  const int grp = (int)uni((uint32_t)(tid >> 8)), t = tid & 255;  // a group is whole wavefronts
-  // thread t of a group owns words t, t + 256 and, for t < 112, t + 512, so
-  // that the 64 lanes of every LDS read take 64 consecutive words (no bank
-  // conflicts: two words per lane at stride two halved the LDS rate)
-  const bool hi = t < 112;
+  const int team = (int)uni((uint32_t)(tid >> 8)), t = tid & 255;  // a team is whole wavefronts
+  // thread t of a team owns words t, t + 256 and t + 512 < 629, so that the 64
+  // lanes of every LDS read take 64 consecutive words
+  const bool hi = t + 512 < kJumpSpan;
+  auto pattern = [&](int b) {
+    const int e = kJumpQ * b;
+    const uint64_t w = (uint64_t)coef[e >> 5] | ((uint64_t)coef[(e >> 5) + 1] << 32);
+    return (uint32_t)(w >> (e & 31)) & (uint32_t)(kJumpPatterns - 1);
+  };
   for (uint32_t r = blockIdx.x; r < n; r += gridDim.x) {
     const TableRow& rw = rows[list[2 * r]];
     const uint32_t j = list[2 * r + 1];  // >= 1
     const uint32_t* src = rw.state + rw.si * kMtStride;
     uint32_t* dst = rw.jstate + (j - 1u) * kMtStride;
+    const uint32_t* jd = rw.jump + (j - 1u) * rw.jstride;
+    const uint32_t nbits = min(uni(jd[0]), 19937u);
     for (int i = tid; i < 624; i += kJumpThreads) seq[i] = src[i];
+    for (int i = tid; i < 625; i += kJumpThreads) coef[i] = 0u;
+    for (int i = kMtSeqWords + tid; i < kJumpZero + kJumpPitch; i += kJumpThreads) seq[i] = 0u;
+    for (int i = tid; i < kJumpList; i += kJumpThreads) groups[i] = (uint16_t)kJumpZero;
+    if (tid < kJumpPatterns) cursor[tid] = 0u;
     __syncthreads();
+    for (uint32_t q = tid; q < nbits; q += kJumpThreads) {
+      const uint32_t e = min((jd[1 + (q >> 1)] >> (16u * (q & 1u))) & 0xFFFFu, 19936u);
+      atomicOr(&coef[e >> 5], 1u << (e & 31));
+    }
     for (int n0 = 624; n0 < kMtSeqWords; n0 += 227) {
       const int x = n0 + tid;
       if (tid < 227 && x < kMtSeqWords) {
@@ -164,84 +196,64 @@ __global__ __launch_bounds__(kJumpThreads) void k_table_mt_jump(const uint32_t* 
       }
       __syncthreads();
     }
-    // group g takes exponents 8 (4m + g) .. 8 (4m + g) + 7; the four words
-    // holding the next eight are fetched one round ahead
-    const uint32_t* jd = rw.jump + (j - 1u) * rw.jstride;
-    const uint32_t nbits = min(uni(jd[0]), 19937u);
-    const uint32_t nfull = nbits / 8u;  // complete groups of eight
-    uint32_t a0 = 0, a1 = 0, a2 = 0;
-    uint32_t gq = (uint32_t)grp;
-    uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-    // (vector loads: their wait is at the next round's first use, and it
-    // does not hold up the LDS reads in between)
-    if (gq < nfull) {
-      w0 = jd[1 + 4 * gq];
-      w1 = jd[2 + 4 * gq];
-      w2 = jd[3 + 4 * gq];
-      w3 = jd[4 + 4 * gq];
-    }
-    for (; gq < nfull; gq += 4u) {
-      const uint32_t u0 = uni(w0), u1 = uni(w1), u2 = uni(w2), u3 = uni(w3);
-      const int ix[8] = {min((int)(u0 & 0xFFFFu), 19936), min((int)(u0 >> 16), 19936),
-                         min((int)(u1 & 0xFFFFu), 19936), min((int)(u1 >> 16), 19936),
-                         min((int)(u2 & 0xFFFFu), 19936), min((int)(u2 >> 16), 19936),
-                         min((int)(u3 & 0xFFFFu), 19936), min((int)(u3 >> 16), 19936)};
-      if (gq + 4u < nfull) {
-        const uint32_t* nx = jd + 1 + 4 * (gq + 4u);
-        w0 = nx[0];
-        w1 = nx[1];
-        w2 = nx[2];
-        w3 = nx[3];
+    // the groups sorted by pattern, every pattern's padded to whole rounds
+    for (int b = tid; b < kJumpGroups; b += kJumpThreads) atomicAdd(&cursor[pattern(b)], 1u);
+    __syncthreads();
+    if (tid < kJumpPatterns) {  // wavefront 0
+      const uint32_t c = tid == 0 ? 0u : (cursor[tid] + kJumpRound - 1u) / kJumpRound * kJumpRound;
+      uint32_t at = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)at, o);
+        if (tid >= o) at += v;
       }
-      uint32_t v0[8], v1[8];
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const uint32_t* p = seq + ix[b] + t;
-        v0[b] = p[0];
-        v1[b] = p[256];
-      }
-      if (hi) {
-        uint32_t v2[8];
-#pragma unroll
-        for (int b = 0; b < 8; ++b) v2[b] = seq[ix[b] + t + 512];
-#pragma unroll
-        for (int b = 0; b < 8; ++b) a2 ^= v2[b];
-      }
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        a0 ^= v0[b];
-        a1 ^= v1[b];
-      }
-    }
-    if (grp == 0) {  // the last nbits % 8 exponents
-      for (uint32_t q = nfull * 8u; q < nbits; ++q) {
-        const int i = min((int)((uni(jd[1 + (q >> 1)]) >> (16u * (q & 1u))) & 0xFFFFu), 19936);
-        const uint32_t* p = seq + i + t;
-        a0 ^= p[0];
-        a1 ^= p[256];
-        if (hi) a2 ^= p[512];
-      }
-    }
-    if (grp > 0) {
-      uint32_t* pp = part[grp - 1];
-      pp[t] = a0;
-      pp[t + 256] = a1;
-      if (hi) pp[t + 512] = a2;
+      first[tid + 1] = at;
+      cursor[tid] = at - c;
+      if (tid == 0) first[0] = 0u;
     }
     __syncthreads();
-    if (grp == 0) {
-#pragma unroll
-      for (int g = 0; g < 3; ++g) {
-        a0 ^= part[g][t];
-        a1 ^= part[g][t + 256];
-        if (hi) a2 ^= part[g][t + 512];
-      }
-      dst[t] = a0;
-      dst[t + 256] = a1;
-      if (hi) dst[t + 512] = a2;
-      if (t == 0) dst[624] = 624u;
+    for (int b = tid; b < kJumpGroups; b += kJumpThreads) {
+      const uint32_t w = pattern(b);
+      if (w) groups[atomicAdd(&cursor[w], 1u)] = (uint16_t)(kJumpQ * b);
     }
-    __syncthreads();  // seq and part are rebuilt for the next segment
+    __syncthreads();
+    uint32_t B[kJumpQ][3] = {};
+    for (uint32_t w = 1; w < (uint32_t)kJumpPatterns; ++w) {
+      const uint32_t end = uni(first[w + 1]);
+      uint32_t a0 = 0, a1 = 0, a2 = 0;
+      for (uint32_t i = uni(first[w]) + 4u * (uint32_t)team; i < end; i += kJumpRound) {
+        const v2u g = *reinterpret_cast<const v2u*>(groups + i);
+        const uint32_t g0 = uni(g.x), g1 = uni(g.y);
+        const uint32_t* p[4] = {seq + (g0 & 0xFFFFu) + t, seq + (g0 >> 16) + t, seq + (g1 & 0xFFFFu) + t,
+                                seq + (g1 >> 16) + t};
+        a0 ^= p[0][0] ^ p[1][0] ^ p[2][0] ^ p[3][0];
+        a1 ^= p[0][256] ^ p[1][256] ^ p[2][256] ^ p[3][256];
+        if (hi) a2 ^= p[0][512] ^ p[1][512] ^ p[2][512] ^ p[3][512];
+      }
+#pragma unroll
+      for (int q = 0; q < kJumpQ; ++q) {
+        const uint32_t m = 0u - ((w >> q) & 1u);
+        B[q][0] ^= a0 & m;
+        B[q][1] ^= a1 & m;
+        B[q][2] ^= a2 & m;
+      }
+    }
+    __syncthreads();  // the sequence is read
+#pragma unroll
+    for (int q = 0; q < kJumpQ; ++q) {
+      uint32_t* s = seq + (team * kJumpQ + q) * kJumpPitch + t;
+      s[0] = B[q][0];
+      s[256] = B[q][1];
+      if (hi) s[512] = B[q][2];
+    }
+    __syncthreads();
+    if (tid < 624) {
+      uint32_t v = 0;
+#pragma unroll
+      for (int q = 0; q < 4 * kJumpQ; ++q) v ^= seq[q * kJumpPitch + tid + q % kJumpQ];
+      dst[tid] = v;
+      if (tid == 0) dst[624] = 624u;
+    }
+    __syncthreads();  // everything is rebuilt for the next segment
   }
 }
 
@@ -271,8 +283,8 @@ hipError_t launch_table_lane(int cls, const TableTask* tasks, uint32_t ntasks, c
                              const uint32_t* tails, uint32_t* counter, const uint32_t* aux, int grid, hipStream_t s) {
   if (cls == 0)
     hipLaunchKernelGGL(k_table_lane, dim3(grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter, aux);
-  else  // RANMAR: eight blocks per CU, a wavefront per segment
-    hipLaunchKernelGGL(k_table_ranmar, dim3(8 * grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter);
+  else  // RANMAR: a wavefront per segment, up to sixteen blocks per CU
+    hipLaunchKernelGGL(k_table_ranmar, dim3(16 * grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter);
   return hipGetLastError();
 }
 
