@@ -1518,6 +1518,15 @@ __device__ __forceinline__ uint32_t mt_temper(uint32_t t) {
   return t;
 }
 
+// One word of the twist: old words a = x_i and b = x_{i+1}, x = x_{i+397}.
+// y takes the upper bit of a and the lower 31 of b, so its bit 0 is b's; that
+// bit spread over the word selects the constant (five instructions in all).
+__device__ __forceinline__ uint32_t mt_twist_word(uint32_t a, uint32_t b, uint32_t x) {
+  const uint32_t y = __builtin_amdgcn_bitop3_b32(a, b, kMtUpper, kLutSelect);
+  const uint32_t odd = (uint32_t)__builtin_amdgcn_sbfe((int)b, 0, 1);
+  return __builtin_amdgcn_bitop3_b32(x ^ (y >> 1), odd, kMtA, kLutXorAnd);
+}
+
 // Cooperative block twist of one stream by one wavefront: round r updates
 // words 64r .. 64r+63 in place.  Word i reads words i and i+1 before the
 // block's update (i+1 in the same or the next round) and word i+397, or for
@@ -1543,10 +1552,7 @@ __device__ __forceinline__ void mt_twist(uint32_t* mt, int lane) {
     for (int q = 0; q < 3; ++q) {
       const int i = (r0 + q) * 64 + lane;
       if (r0 + q < 10 && i < 624) {
-        // y = upper bit of a, lower 31 bits of b (one select instruction);
-        // bit 0 of y is bit 0 of b
-        const uint32_t y = __builtin_amdgcn_bitop3_b32(a[q], b[q], kMtUpper, kLutSelect);
-        mt[i] = x[q] ^ (y >> 1) ^ ((b[q] & 1u) ? kMtA : 0u);
+        mt[i] = mt_twist_word(a[q], b[q], x[q]);
       }
     }
     wave_sync();
@@ -1580,8 +1586,7 @@ __device__ __forceinline__ void mt_twist_emit(uint32_t* mt, int lane, E& emit) {
     uint32_t nw[3], old[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const uint32_t y = __builtin_amdgcn_bitop3_b32(a[q], b[q], kMtUpper, kLutSelect);
-      nw[q] = x[q] ^ (y >> 1) ^ ((b[q] & 1u) ? kMtA : 0u);
+      nw[q] = mt_twist_word(a[q], b[q], x[q]);
       old[q] = a[q];
     }
     wave_sync();  // every read of the group before any of its writes
@@ -1653,8 +1658,7 @@ __device__ __forceinline__ void mt_twist_block(uint32_t* mt, int tid) {
     }
     __syncthreads();
     if (on) {
-      const uint32_t y = __builtin_amdgcn_bitop3_b32(a, b, kMtUpper, kLutSelect);
-      mt[i] = x ^ (y >> 1) ^ ((b & 1u) ? kMtA : 0u);
+      mt[i] = mt_twist_word(a, b, x);
     }
     __syncthreads();
   }

@@ -138,13 +138,18 @@ __global__ __launch_bounds__(W == 16 ? 1024 : 256) void k_split_fused(uint32_t* 
 
 // Emitter of mt_twist_emit for the fused consumer: the draw's top 24 bits
 // (the f32 value times 2^24) into the lane's sum and the wave's histogram.
+// The histogram has kMtCols columns of 64 bins (lane l counts in column
+// l mod kMtCols; one pad word per bin): with a single one, 32 lanes of random
+// bins cost five extra LDS cycles per draw of a wavefront, a third of the LDS
+// time, which bounds the kernel beside VALU issue.
+constexpr int kMtCols = 8, kMtHistPitch = kMtCols + 1;
 struct MtFusedEmit {
-  uint32_t* h;
+  uint32_t* h;  // the lane's column
   uint32_t part;
   __device__ __forceinline__ void operator()(int, uint32_t w) {
     const uint32_t k = mt_temper(w) >> 8;
     part += k;
-    __hip_atomic_fetch_add(&h[k >> 18], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_fetch_add(&h[(k >> 18) * kMtHistPitch], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
   }
 };
 
@@ -152,15 +157,16 @@ __global__ __launch_bounds__(256) void k_mt_fused(uint32_t* __restrict__ state, 
                                                   uint64_t* __restrict__ sum, uint32_t* __restrict__ hist,
                                                   int accumulate) {
   __shared__ uint32_t mt_all[4][624];
-  __shared__ uint32_t h_all[4][64];
+  __shared__ uint32_t h_all[4][64 * kMtHistPitch];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint64_t s = (uint64_t)blockIdx.x * 4u + w;
   if (s >= n) return;
   uint32_t* mt = mt_all[w];
-  uint32_t* h = h_all[w];
+  uint32_t* const h = h_all[w];
+  uint32_t* const col = h + (lane & (kMtCols - 1));
   uint32_t* sp = state + s * kMtStride;
   for (int i = lane; i < 624; i += 64) mt[i] = sp[i];
-  h[lane] = 0;
+  for (int i = lane; i < 64 * kMtHistPitch; i += 64) h[i] = 0;
   uint32_t pos = uni(sp[624]);
   wave_sync();
   uint32_t done = 0;
@@ -173,7 +179,7 @@ __global__ __launch_bounds__(256) void k_mt_fused(uint32_t* __restrict__ state, 
     if (pos == 0u && draws - done > 624u) {
       // a whole block with draws after it: consumed during the twist that
       // makes the next block
-      MtFusedEmit emit{h, 0u};
+      MtFusedEmit emit{col, 0u};
       mt_twist_emit(mt, lane, emit);
       acc += emit.part;
       done += 624u;
@@ -184,7 +190,7 @@ __global__ __launch_bounds__(256) void k_mt_fused(uint32_t* __restrict__ state, 
     for (uint32_t j = lane; j < m; j += 64) {
       const uint32_t k = mt_temper(mt[pos + j]) >> 8;
       part += k;
-      __hip_atomic_fetch_add(&h[k >> 18], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+      __hip_atomic_fetch_add(&col[(k >> 18) * kMtHistPitch], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
     acc += part;
     pos += m;
@@ -197,7 +203,10 @@ __global__ __launch_bounds__(256) void k_mt_fused(uint32_t* __restrict__ state, 
     sp[624] = pos;
     sum[s] = (accumulate ? sum[s] : 0ull) + acc;
   }
-  hist[s * 64u + lane] = (accumulate ? hist[s * 64u + lane] : 0u) + h[lane];
+  uint32_t hb = 0;
+#pragma unroll
+  for (int c = 0; c < kMtCols; ++c) hb += h[lane * kMtHistPitch + c];
+  hist[s * 64u + lane] = (accumulate ? hist[s * 64u + lane] : 0u) + hb;
 }
 
 template <class G>
