@@ -1566,7 +1566,7 @@ __device__ __forceinline__ void mt_twist(uint32_t* mt, int lane) {
 // table then holds the next block: callers use it only when draws remain
 // after the emitted block.
 template <class E>
-__device__ __forceinline__ void mt_twist_emit(uint32_t* mt, int lane, E& emit) {
+__device__ __forceinline__ void mt_twist_emit(uint32_t* mt, int lane, E&& emit) {
   uint32_t a[3], b[3], x[3];
   auto fetch = [&](int r0) {
 #pragma unroll

@@ -117,6 +117,63 @@ __global__ __launch_bounds__(256) void k_mt_generate(uint32_t* __restrict__ stat
               reinterpret_cast<uint64_t>(out) + ((s0 + 1) * row_elems + elem_off) * es, sp1);
 }
 
+// Emitter of mt_twist_emit for 4-byte rows: word i of the block at `at` + 4 i.
+template <int DT>
+struct MtRowEmit {
+  uint64_t at;
+  __device__ __forceinline__ void operator()(int i, uint32_t w) const {
+    const uint32_t u = mt_temper(w);
+    put<uint32_t>(at + 4ull * (uint32_t)i, DT == U32 ? u : __float_as_uint(mt_f32<DT>(u)));
+  }
+};
+
+template <int DT>
+__device__ __forceinline__ void mt_row_wave(uint32_t* mt, int lane, uint32_t& pos, uint32_t draws, uint64_t row) {
+  uint32_t done = 0;
+  while (done < draws) {
+    if (pos >= 624u) {
+      mt_twist(mt, lane);
+      pos = 0;
+    }
+    const MtRowEmit<DT> emit{row + 4ull * done};
+    if (pos == 0u && draws - done > 624u) {
+      // a whole block with draws after it: stored during the twist that makes the next block
+      mt_twist_emit(mt, lane, emit);
+      done += 624u;
+      continue;
+    }
+    const uint32_t m = min(624u - pos, draws - done);
+    for (uint32_t j = (uint32_t)lane; j < m; j += 64u) emit((int)j, mt[pos + j]);
+    pos += m;
+    done += m;
+  }
+}
+
+// One stream per wavefront, its words stored straight from the twist that
+// consumes them (256 bytes of the row per store): no barriers, and 17 VALU
+// instructions per 64 draws where k_mt_generate, whose phases and stores fill
+// 227 and 156 of 256 lanes, takes 25.  f32: 10007 x 1537 31 -> 23 us, 16384 x
+// 4096 74 -> 62 us, 65536 x 300 85 -> 68 us, 256 x 4096 12.2 -> 8.6 us.
+template <int DT>
+__global__ __launch_bounds__(256) void k_mt_wave(uint32_t* __restrict__ state, uint64_t n, uint32_t draws,
+                                                 void* __restrict__ out, uint64_t row_elems, uint64_t elem_off) {
+  static_assert(DT != F64, "an fp64 element takes the words of two lanes");
+  __shared__ uint32_t mt_all[4][624];
+  const int lane = threadIdx.x & 63;
+  const uint64_t s = (uint64_t)blockIdx.x * 4u + (threadIdx.x >> 6);
+  if (s >= n) return;  // whole wavefront; no block-wide barrier is used
+  uint32_t* mt = mt_all[threadIdx.x >> 6];
+  uint32_t* sp = state + s * kMtStride;
+  for (int i = lane; i < 624; i += 64) mt[i] = sp[i];
+  uint32_t pos = uni(sp[624]);
+  wave_sync();
+  const uint64_t row = reinterpret_cast<uint64_t>(out) + (s * row_elems + elem_off) * 4ull;
+  mt_row_wave<DT>(mt, lane, pos, draws, row);
+  wave_sync();
+  for (int i = lane; i < 624; i += 64) sp[i] = mt[i];
+  if (lane == 0) sp[624] = pos;
+}
+
 // ============================================================ leapfrog kernels
 // Multiplicative and affine generators (GGL, RANECU, DRAND48, RANNYU): one
 // wavefront per stream; lane l produces positions 4 l .. 4 l + 3 of every
@@ -620,6 +677,21 @@ hipError_t launch_generate(int kind, uint32_t p, uint32_t* st, uint64_t n, uint6
     case MT19937: {
       const dim3 grid((unsigned)((n + 1) / 2)), block(256);
       const uint32_t d = (uint32_t)draws;
+      // Long launches are bound by their stores and gain from few rows being
+      // written at a time, a workgroup's each (65536 x 16384 f32 969 us, one
+      // row per wavefront 1016 us); all others run one stream per wavefront.
+      if (dtype != F64 && (n < 32768 || draws < 4096)) {
+        const dim3 gw((unsigned)((n + 3) / 4));
+        if (dtype == U32)
+          hipLaunchKernelGGL((k_mt_wave<U32>), gw, block, 0, s, st, n, d, out, row_elems, off);
+        else if (dtype == F32)
+          hipLaunchKernelGGL((k_mt_wave<F32>), gw, block, 0, s, st, n, d, out, row_elems, off);
+        else if (dtype == F32P)
+          hipLaunchKernelGGL((k_mt_wave<F32P>), gw, block, 0, s, st, n, d, out, row_elems, off);
+        else
+          return hipErrorInvalidValue;
+        return hipGetLastError();
+      }
       switch (dtype) {
         case U32:
           hipLaunchKernelGGL((k_mt_generate<U32>), grid, block, 0, s, st, n, d, out, row_elems, off);
