@@ -12,7 +12,12 @@
 //
 // Layout of the work
 // ------------------
-// * GGL, XOR128, RANECU, RANMAR, RANLUX, DRAND48, RANNYU: one lane per stream
+// * GGL, RANECU, DRAND48, RANNYU: plain rows leap, a wavefront per stream
+//   (k_plain.hip); RANMAR and MT19937 keep a stream's window in LDS and step it
+//   with a wavefront (RanmarWave, mt_twist_emit) or, for long MT19937 launches,
+//   a workgroup.
+// * XOR128 and RANLUX, and the other lane kinds in the stream table and where
+//   their streams fill the chip: one lane per stream
 //   (Section 3.1: independent sequences, one lag table per instance).  The
 //   whole lag table lives in VGPRs (1, 4, 2, 97+1, 24+2 and 2 words) and is read from HBM once per
 //   launch and written back once.  Tables with more than one lag (RANMAR,
@@ -25,10 +30,10 @@
 //   stage[(j >> 1) * 130 + 2 l + (j & 1)]); the wave then stores the chunk row
 //   by row, each lane writing 8 bytes, so one store instruction writes up to
 //   512 contiguous bytes of one stream instead of 64 scattered words.
-// * MT19937: one wavefront per stream.  Its 624-word state (2.5 KB) sits in
-//   LDS and the 64 lanes twist it cooperatively in ten rounds of 64 words
-//   (words >= 227 read values made at least three rounds earlier), then
-//   temper and store a block of 624 outputs with fully coalesced row stores.
+// * MT19937: the 624-word state (2.5 KB) sits in LDS and is twisted
+//   cooperatively, by 64 lanes in ten rounds of 64 words (words >= 227 read
+//   values made at least three rounds earlier) or by 256 threads in three
+//   phases, then tempered and stored with coalesced row stores.
 //   The paper had to keep this table in global memory because 128 registers
 //   per thread could not hold it (Section 3.7).
 // * Segments (not in the paper): a long stream can be cut into segments that
@@ -68,8 +73,8 @@ typedef __attribute__((address_space(1))) double gf64;
 // Output store of one element (or vector) at byte address `addr`.  NT makes
 // it non-temporal: the line streams past the caches.  Measured on the full
 // plain launches, that pays where much ALU and LDS work sits between the
-// stores (MT19937: 7-10% faster; RANECU's leapfrog kernel: 3%) and costs 1-5%
-// in the store-bound lane kernels, so each kernel picks.
+// stores (long MT19937 launches: 7-10% faster; RANECU's aligned rows: 3%) and
+// costs 1-5% in the store-bound lane kernels, so each kernel picks.
 // A dword-aligned address is enough for a vector store to global memory (an LDS
 // access needs its full alignment).
 template <class T, bool NT = false>
