@@ -165,6 +165,9 @@ constexpr uint32_t kLuxSplitMax = 64;
 hipError_t launch_lux_fused_split(uint32_t p, uint32_t* st, const uint32_t* snap, uint64_t n, uint64_t draws,
                                   uint32_t S, uint32_t K, const uint32_t* digits, const uint32_t* aux, uint64_t* sum,
                                   uint32_t* hist, bool acc, hipStream_t s);
+// A launch holds less than 2^32 threads: beyond this many streams a stream gets
+// a lane instead of a wavefront.
+constexpr uint64_t kWaveStreams = 1ull << 25;
 // From this many streams on, one lane per stream keeps the SIMDs busy by
 // itself and XOR128's segments are few and long (128-draw chunks).
 constexpr uint64_t kXorLanes = 32768;

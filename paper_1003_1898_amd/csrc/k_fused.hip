@@ -230,6 +230,7 @@ int split_width(uint64_t n, uint64_t draws, double jump, bool pow2) {
   double best = 2.0 * (double)draws * std::ceil(rounds((double)((n + 63) / 64))) + 40.0;
   int width = 0;
   for (int W : {1, 4, 16}) {
+    if (n > kWaveStreams / W) break;
     const int bits = W == 1 ? 6 : W == 4 ? 8 : 10;
     uint64_t S = (draws + 64ull * W - 1) / (64ull * W);
     if (pow2) S = std::bit_ceil(S);
@@ -281,6 +282,7 @@ hipError_t launch_fused(int kind, uint32_t p, uint32_t* st, uint64_t n, uint64_t
     case RANECU:
       return launch_split_fused<Ranecu<kSplitT>, Ranecu<>>(st, n, draws, sum, hist, acc, s);
     case RANMAR:
+      if (n > kWaveStreams) return launch_lane_fused<Ranmar<>>(p, st, n, draws, sum, hist, acc, s);
       return launch_ranmar_fused(st, n, draws, sum, hist, acc, s);
     case RANLUX:
       return launch_lane_fused<Ranlux<>>(p, st, n, draws, sum, hist, acc, s);

@@ -582,16 +582,6 @@ hipError_t launch_leap_pack_w(int dtype, uint32_t* st, uint64_t n, uint64_t draw
   return hipGetLastError();
 }
 
-// wavefronts per row of four streams: about 4096 in all, none without a position
-template <class G>
-hipError_t launch_leap_pack(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
-                            uint64_t off, hipStream_t s) {
-  const uint64_t want = std::min((4096 + n / 4 - 1) / (n / 4), (draws + 63) / 64);
-  if (want >= 16) return launch_leap_pack_w<G, 16>(dtype, st, n, draws, out, row_elems, off, s);
-  if (want >= 4) return launch_leap_pack_w<G, 4>(dtype, st, n, draws, out, row_elems, off, s);
-  return launch_leap_pack_w<G, 1>(dtype, st, n, draws, out, row_elems, off, s);
-}
-
 template <class G>
 hipError_t launch_lane_pack(int dtype, uint32_t p, uint32_t* st, uint64_t n, uint64_t draws, void* out,
                             uint64_t row_elems, uint64_t off, hipStream_t s) {
@@ -614,6 +604,17 @@ hipError_t launch_lane_pack(int dtype, uint32_t p, uint32_t* st, uint64_t n, uin
       return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+// wavefronts per row of four streams: about 4096 in all, none without a position
+template <class G>
+hipError_t launch_leap_pack(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
+                            uint64_t off, hipStream_t s) {
+  if (n > kWaveStreams) return launch_lane_pack<G>(dtype, 0u, st, n, draws, out, row_elems, off, s);
+  const uint64_t want = std::min((4096 + n / 4 - 1) / (n / 4), (draws + 63) / 64);
+  if (want >= 16) return launch_leap_pack_w<G, 16>(dtype, st, n, draws, out, row_elems, off, s);
+  if (want >= 4) return launch_leap_pack_w<G, 4>(dtype, st, n, draws, out, row_elems, off, s);
+  return launch_leap_pack_w<G, 1>(dtype, st, n, draws, out, row_elems, off, s);
 }
 
 template <class G>
