@@ -279,14 +279,17 @@ struct StageSink {  // generation: draw j of the chunk goes to the wave's stage
   __device__ __forceinline__ void operator()(int j, uint32_t u) { st.put(lane, j, u); }
 };
 
-template <int BITS, int PITCH = kPitch>
-struct FusedSink {  // in-kernel consumer: mantissa sum and 64-bin histogram
+// In-kernel consumer: mantissa sum and 64-bin histogram.  SCOPE spans the lanes
+// that count in the histogram: a wavefront's own, or the workgroup's (the same
+// LDS instruction, but the compiler must not take the word for one wavefront's).
+template <int BITS, int PITCH = kPitch, int SCOPE = __HIP_MEMORY_SCOPE_WAVEFRONT>
+struct FusedSink {
   uint32_t acc;
   uint32_t* hcol;
   __device__ __forceinline__ void operator()(int, uint32_t u) {
     uint32_t k = u >> (BITS - 24);
     acc += k;
-    __hip_atomic_fetch_add(&hcol[(k >> 18) * PITCH], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_fetch_add(&hcol[(k >> 18) * PITCH], 1u, __ATOMIC_RELAXED, SCOPE);
   }
 };
 

@@ -104,7 +104,8 @@ __global__ __launch_bounds__(W == 16 ? 1024 : 256) void k_split_fused(uint32_t* 
   }
   if constexpr (W > 1) __syncthreads();  // the histogram is clear, every wavefront has read the state
   wave_sync();
-  FusedSink<G::BITS, kHistPitch> sink{0u, h + (lane & 31)};
+  FusedSink<G::BITS, kHistPitch, W == 1 ? __HIP_MEMORY_SCOPE_WAVEFRONT : __HIP_MEMORY_SCOPE_WORKGROUP> sink{
+      0u, h + (lane & 31)};
   uint64_t total = 0;
   uint32_t i = 0;
   for (; i + kSplitT <= cnt; i += kSplitT) {
