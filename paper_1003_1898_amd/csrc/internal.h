@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "routes.h"
+
 namespace prng {
 
 enum Kind : int { GGL = 1, XOR128 = 2, RANECU = 3, RANMAR = 4, RANLUX = 5, MT19937 = 6, DRAND48 = 7, RANNYU = 8 };
@@ -168,9 +170,6 @@ hipError_t launch_lux_fused_split(uint32_t p, uint32_t* st, const uint32_t* snap
 // A launch holds less than 2^32 threads: beyond this many streams a stream gets
 // a lane instead of a wavefront.
 constexpr uint64_t kWaveStreams = 1ull << 25;
-// From this many streams on, one lane per stream keeps the SIMDs busy by
-// itself and XOR128's segments are few and long (128-draw chunks).
-constexpr uint64_t kXorLanes = 32768;
 // XOR128 plain generation with every stream cut into K >= 2 segments of S
 // positions (a multiple of 128), 256 streams per block and segment, so that
 // several wavefronts per SIMD share the stores.  snap: copy of the state

@@ -749,7 +749,8 @@ hipError_t launch_xor128_chunks(uint32_t* st, const uint32_t* snap, uint64_t n, 
 hipError_t launch_xor128_split(uint32_t* st, const uint32_t* snap, uint64_t n, uint64_t draws, int dtype, uint32_t S,
                                uint32_t K, const uint32_t* pow2, void* out, uint64_t row_elems, uint64_t off,
                                hipStream_t s) {
-  if (n >= kXorLanes) return launch_xor128_chunks<128>(st, snap, n, draws, dtype, S, K, pow2, out, row_elems, off, s);
+  if (xor128_long_segments(n, draws))
+    return launch_xor128_chunks<128>(st, snap, n, draws, dtype, S, K, pow2, out, row_elems, off, s);
   return launch_xor128_chunks<64>(st, snap, n, draws, dtype, S, K, pow2, out, row_elems, off, s);
 }
 

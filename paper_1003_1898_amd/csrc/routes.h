@@ -1,0 +1,58 @@
+// Which kernel a call takes and how its streams are cut: rules on stream and
+// draw counts, on the host.
+#pragma once
+#include <algorithm>
+#include <bit>
+#include <cstdint>
+
+namespace prng {
+
+// Output up to about this many bytes stays in the 256 MB last-level cache,
+// whatever order its rows are stored in; more of it is bound by that order.
+constexpr uint64_t kCachedBytes = 320'000'000;
+
+// A stream's draws cut into K segments of S (the last one shorter); K = 1: uncut.
+struct Cut {
+  uint64_t S, K;
+};
+
+// ---------------------------------------------------------------- XOR128 rows
+// From this many streams on, one lane per stream keeps the SIMDs busy by itself.
+constexpr uint64_t kXorLanes = 32768;
+
+// Few long segments, staged in 128-draw chunks (one workgroup per CU), for many
+// streams and for output beyond the cache; otherwise many short segments in
+// 64-draw chunks (two workgroups per CU).  f32, long and short: 20032 x 4096
+// (328 MB) 80 and 100 us, 12032 x 8192 (394 MB) 85 and 123 us, 24000 x 16384
+// 305 and 331 us; 20032 x 3072 (246 MB) 92 and 48 us, 12032 x 6000 (289 MB) 108
+// and 73 us.  Below 8192 streams long segments leave SIMDs idle (4096 x 32768
+// 149 and 154 us, 1024 x 32768 134 and 44 us).
+inline bool xor128_long_segments(uint64_t n, uint64_t d) {
+  return n >= kXorLanes || (n >= 8192 && 4 * n * d > kCachedBytes);
+}
+
+// d draws of n streams.  Segments start from jumped states.
+// Long segments: at least 2048 draws, about 4096 wavefronts in all.
+// Short ones: about 2048 wavefronts in segments of a power of two from 128 draws
+// on: a jump costs a matrix product (2 us) per set bit of its distance, and the
+// power of two leaves only those of the segment's number.  f64 4096 x 2000 127
+// us uncut, 34 us in 32 segments.  The copy of the states and a jump cost about
+// as much as 200 draws, less where the uncut call would end inside a 128-draw
+// chunk.  Uncut and in segments of 128, f32: 4096 x 256 10.1 and 13.0 us, x 300
+// 15.1 and 14.4, x 384 14.1 and 13.2, x 512 18.1 and 16.4; 20011 x 256 12.1 and
+// 15.0, x 320 17.1 and 15.2, x 512 19.8 and 20.6, x 640 23.4 and 21.2.
+// `shared`: the snapshot area is every call's of the GPU, and short calls leave it alone.
+inline Cut xor128_cut(uint64_t n, uint64_t d, bool shared) {
+  const uint64_t waves = (n + 63) / 64;
+  uint64_t S = d;
+  if (xor128_long_segments(n, d)) {
+    const uint64_t K = std::min<uint64_t>({8, (4096 + waves - 1) / waves, std::max<uint64_t>(1, d / 2048)});
+    S = ((d + K - 1) / K + 127) / 128 * 128;
+  } else if (shared ? d >= 4096 : d > (n < 16384 ? 256u : 512u) || (d > 300 && d % 128 != 0)) {
+    const uint64_t want = 2048 / waves;
+    S = std::max<uint64_t>(128, std::bit_ceil((d + want - 1) / want));
+  }
+  return {S, (d + S - 1) / S};  // (K - 1) S < d: no segment is empty
+}
+
+}  // namespace prng

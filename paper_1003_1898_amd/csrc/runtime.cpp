@@ -6,7 +6,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <bit>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -355,27 +354,8 @@ int generate_with(prng_gen* g, uint64_t count, int dtype, void* d_out, size_t ou
       continue;
     }
     if (g->kind == XOR128) {
-      // Cut each stream into K segments with jumped starts.  From kXorLanes
-      // streams on, one lane per stream comes near to filling the SIMDs and
-      // segments of at least 2048 draws, about 4096 wavefronts in all, run one
-      // workgroup per CU (a 128-draw stage takes 134 KB of LDS).  Below, about
-      // 2048 wavefronts in segments of a power of two from 128 draws on: a
-      // jump costs a matrix product (2 us) per set bit of its distance, and
-      // the power of two leaves only those of the segment's number.  f64 4096
-      // x 2000: 127 us uncut, 34 us in 32 segments; f32 10007 x 1537 88 and 30
-      // us, 65536 x 1024 44 us uncut and 47 us in two.
       const uint64_t d = c * per;
-      const uint64_t waves = (g->n + 63) / 64;
-      uint64_t S;
-      if (g->n < kXorLanes) {
-        const uint64_t want = 2048 / waves;
-        S = shared && d < 4096 ? d : std::max<uint64_t>(128, std::bit_ceil((d + want - 1) / want));
-      } else {
-        const uint64_t K =
-            std::min<uint64_t>({8, (4096 + waves - 1) / waves, std::max<uint64_t>(1, d / 2048)});
-        S = ((d + K - 1) / K + 127) / 128 * 128;
-      }
-      const uint64_t K = (d + S - 1) / S;  // (K - 1) S < d: no segment is empty
+      const auto [S, K] = xor128_cut(g->n, d, shared);
       if (K > 1) {
         HIP_TRY(hipMemcpyAsync(snap_area, g->d_state, state_region_bytes(XOR128, g->n), hipMemcpyDeviceToDevice, s));
         HIP_TRY(launch_xor128_split(g->d_state, snap_area, g->n, d, dtype, (uint32_t)S, (uint32_t)K,

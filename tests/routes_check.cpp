@@ -1,0 +1,19 @@
+// Prints what the dispatch rules of csrc/routes.h choose, one answer per line of standard input.
+#include <cstdio>
+#include <iostream>
+#include <string>
+
+#include "routes.h"
+
+int main() {
+  std::string rule;
+  unsigned long long n, d, x;
+  while (std::cin >> rule >> n >> d >> x) {
+    if (rule == "xor128") {
+      const prng::Cut c = prng::xor128_cut(n, d, x != 0);
+      printf("%llu %llu\n", (unsigned long long)c.S, (unsigned long long)c.K);
+    } else {
+      return 1;
+    }
+  }
+}

@@ -1,0 +1,30 @@
+"""Calls at the lines between two ways of running them: draw and stream counts
+on both sides, bit-exact with the oracle."""
+import numpy as np
+import pytest
+
+from paper_1003_1898_amd import inputs
+from paper_1003_1898_amd.generator import Generator
+
+from mirror import bits
+
+pytestmark = pytest.mark.gpu
+
+
+def _check_rows(oracle, kind, n, calls, p=223):
+    print(f"\n[routes] {kind} n={n}", flush=True)
+    seeds = inputs.seed_words(kind, 77, n)
+    g = Generator(kind, n, seed_words=seeds, p=p)
+    st = oracle.init(kind, seeds)
+    for count, dt in calls:
+        got = bits(g.generate(count, dt).cpu().numpy())
+        assert np.array_equal(got, bits(oracle.generate(kind, st, count, dt, p=p, threads=8))), f"{count} {dt}"
+        assert np.array_equal(g.state_words(), st), f"state after {count} {dt}"
+
+
+@pytest.mark.parametrize("n,calls", [(1000, ((256, "f32"), (257, "u32"), (150, "f64"))),
+                                     (16384, ((512, "u32"), (513, "f32"), (301, "f32"), (300, "u32"))),
+                                     (8200, ((9200, "f32"), (4601, "f64"))),  # beyond the cache: long segments
+                                     (24001, ((3200, "u32"),))])
+def test_xor128_rows(oracle, n, calls):
+    _check_rows(oracle, "xor128", n, calls)

@@ -1,0 +1,59 @@
+"""The dispatch rules of csrc/routes.h on the CPU: calls that one way of running
+them was measured to be slower for take the other one, and every answer is one
+that the kernels accept."""
+import os
+import random
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_1003_1898_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("routes") / "routes_check")
+    subprocess.run(["g++", "-O1", "-std=c++20", "-I", CSRC, os.path.join(HERE, "routes_check.cpp"), "-o", exe],
+                   check=True)
+
+    def ask(rule, calls):
+        """The rule's answers (lists of integers) to calls of three numbers."""
+        text = "".join("%s %d %d %d\n" % (rule, *c) for c in calls)
+        out = subprocess.run([exe], input=text, check=True, capture_output=True, text=True).stdout
+        return [[int(v) for v in line.split()] for line in out.splitlines()]
+
+    return ask
+
+
+def _calls(seed, count, n_max, d_max, third):
+    r = random.Random(seed)
+    return [(int(2 ** r.uniform(0, n_max)), int(2 ** r.uniform(0, d_max)), r.choice(third)) for _ in range(count)]
+
+
+# ------------------------------------------------------------------ XOR128 rows
+@pytest.mark.parametrize("n,d", [(64, 256), (256, 200), (4096, 256), (10007, 160), (20011, 512), (28000, 384),
+                                 (32000, 512)])
+def test_xor128_short_calls_stay_uncut(routes, n, d):
+    assert routes("xor128", [(n, d, 0)])[0][1] == 1
+
+
+@pytest.mark.parametrize("n,d,K", [(256, 384, 3), (4096, 512, 4), (4096, 4000, 32), (20011, 448, 4), (20011, 2048, 4),
+                                   (1024, 32768, 128)])
+def test_xor128_short_segments(routes, n, d, K):
+    S, got = routes("xor128", [(n, d, 0)])[0]
+    assert got == K and S & (S - 1) == 0
+
+
+@pytest.mark.parametrize("n,d,K", [(12032, 8192, 4), (20032, 4096, 2), (24000, 16384, 8), (28000, 4096, 2),
+                                   (32768, 1500, 1), (65536, 16384, 4)])
+def test_xor128_output_beyond_the_cache_takes_long_segments(routes, n, d, K):
+    assert routes("xor128", [(n, d, 0)])[0][1] == K
+
+
+def test_xor128_cuts_are_whole(routes):
+    calls = _calls(1, 4000, 20, 30, (0, 1))
+    for (n, d, shared), (S, K) in zip(calls, routes("xor128", calls)):
+        assert (K - 1) * S < d <= K * S, (n, d, shared)
+        assert K == 1 or (S % 128 == 0 and K * ((n + 255) // 256) < 1 << 24), (n, d, shared)
+        assert not shared or d >= 4096 or K == 1, (n, d)
