@@ -163,7 +163,6 @@ hipError_t launch_lux_plain(uint32_t p, uint32_t* st, const uint32_t* snap, uint
 // RANLUX in-kernel consumer with every stream cut into K segments of S
 // positions (a multiple of 24; 2 <= K <= kLuxSplitMax), one wavefront per
 // stream.  snap, digits and aux as for launch_lux_plain.
-constexpr uint32_t kLuxSplitMax = 64;
 hipError_t launch_lux_fused_split(uint32_t p, uint32_t* st, const uint32_t* snap, uint64_t n, uint64_t draws,
                                   uint32_t S, uint32_t K, const uint32_t* digits, const uint32_t* aux, uint64_t* sum,
                                   uint32_t* hist, bool acc, hipStream_t s);

@@ -326,24 +326,8 @@ int generate_with(prng_gen* g, uint64_t count, int dtype, void* d_out, size_t ou
   for (uint64_t off = 0; off < count; off += max_elems) {
     const uint64_t c = count - off < max_elems ? count - off : max_elems;
     if (g->kind == RANLUX) {
-      // The borrow chain runs one step at a time per lane; the kernel needs
-      // two wavefronts per SIMD to overlap it with the stores.  Cut each
-      // stream into K segments (jumped starts): about 2048 wavefronts where a
-      // segment keeps 1536 draws, and about 1024, one per SIMD, in segments
-      // from 96 draws on otherwise.  A jump takes as long as about 100 draws,
-      // less than the segments save: p = 97, 20011 streams x 1001, 69 us in
-      // one segment, 44 us in four of 288 (47 us in eight of 192); 300 x 5000
-      // 107 and 31 us.
       const uint64_t d = c * per;
-      const uint64_t waves = (g->n + 63) / 64;
-      uint64_t K = std::min<uint64_t>({kLuxSplitMax, (2048 + waves - 1) / waves, std::max<uint64_t>(1, d / 1536)});
-      if (!shared)
-        K = std::max(K, std::min<uint64_t>({kLuxSplitMax, (1024 + waves - 1) / waves, std::max<uint64_t>(1, d / 96)}));
-      uint64_t S = d;
-      if (K > 1) {
-        S = ((d + K - 1) / K + 95) / 96 * 96;
-        K = (d + S - 1) / S;  // (K - 1) S < d: no segment is empty
-      }
+      const auto [S, K] = lux_cut(g->n, d, g->p, shared);
       uint32_t* snap = g->d_state;
       if (K > 1) {
         snap = snap_area;

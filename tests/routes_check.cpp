@@ -12,6 +12,9 @@ int main() {
     if (rule == "xor128") {
       const prng::Cut c = prng::xor128_cut(n, d, x != 0);
       printf("%llu %llu\n", (unsigned long long)c.S, (unsigned long long)c.K);
+    } else if (rule == "lux" || rule == "lux_shared") {
+      const prng::Cut c = prng::lux_cut(n, d, (uint32_t)x, rule == "lux_shared");
+      printf("%llu %llu\n", (unsigned long long)c.S, (unsigned long long)c.K);
     } else {
       return 1;
     }

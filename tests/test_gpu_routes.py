@@ -28,3 +28,12 @@ def _check_rows(oracle, kind, n, calls, p=223):
                                      (24001, ((3200, "u32"),))])
 def test_xor128_rows(oracle, n, calls):
     _check_rows(oracle, "xor128", n, calls)
+
+
+@pytest.mark.parametrize("n,p,calls", [(70, 24, ((492, "u32"), (242, "f64"), (480, "f32"))),
+                                       (300, 97, ((240, "f32"), (241, "u32"), (180, "f64"))),
+                                       (130, 389, ((192, "u32"), (193, "f32"), (101, "f64"))),
+                                       (16500, 97, ((520, "f32"), (470, "u32"))),
+                                       (32800, 223, ((500, "f32"), (390, "u32"), (120, "f64")))])
+def test_ranlux_rows(oracle, n, p, calls):
+    _check_rows(oracle, "ranlux", n, calls, p)

@@ -57,3 +57,26 @@ def test_xor128_cuts_are_whole(routes):
         assert (K - 1) * S < d <= K * S, (n, d, shared)
         assert K == 1 or (S % 128 == 0 and K * ((n + 255) // 256) < 1 << 24), (n, d, shared)
         assert not shared or d >= 4096 or K == 1, (n, d)
+
+
+# ------------------------------------------------------------------ RANLUX rows
+@pytest.mark.parametrize("n,d,p", [(64, 192, 24), (4096, 256, 24), (256, 448, 24), (4096, 256, 97), (20011, 256, 97),
+                                   (40000, 192, 223), (40000, 512, 97), (48000, 2304, 24), (40000, 3000, 97)])
+def test_ranlux_short_calls_stay_uncut(routes, n, d, p):
+    assert routes("lux", [(n, d, p)])[0][1] == 1
+
+
+@pytest.mark.parametrize("n,d,p,K", [(4096, 576, 24, 6), (256, 224, 97, 2), (4096, 384, 97, 4), (64, 224, 389, 2),
+                                     (20011, 1001, 97, 4), (40000, 512, 389, 2), (300, 5000, 97, 27),
+                                     (24000, 3072, 24, 2), (65536, 16384, 223, 2)])
+def test_ranlux_segments(routes, n, d, p, K):
+    assert routes("lux", [(n, d, p)])[0][1] == K
+
+
+@pytest.mark.parametrize("rule", ["lux", "lux_shared"])
+def test_ranlux_cuts_are_whole(routes, rule):
+    calls = _calls(2, 4000, 20, 30, (24, 48, 97, 223, 389, 800))
+    for (n, d, p), (S, K) in zip(calls, routes(rule, calls)):
+        assert (K - 1) * S < d <= K * S and 1 <= K <= 64, (n, d, p)
+        assert K == 1 or (S % 96 == 0 and K * ((n + 255) // 256) < 1 << 24), (n, d, p)
+        assert rule == "lux" or K == 1 or d >= 3072, (n, d)
