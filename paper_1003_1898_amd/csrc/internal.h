@@ -27,6 +27,7 @@ constexpr int kBits[kKinds] = {0, 31, 32, 31, 24, 24, 32, 32, 32};
 // structure-of-arrays order (word j of stream s at state[j*n + s]); MT19937
 // keeps each stream's 625 words contiguous, padded to kMtStride words.
 constexpr int kMtStride = 628;
+static_assert(kMtStateBytes == kMtStride * 4);
 
 inline bool lane_kind(int k) { return (k >= GGL && k <= RANLUX) || k == DRAND48 || k == RANNYU; }
 inline size_t elem_bytes(int dt) { return dt == F64 ? 8 : 4; }

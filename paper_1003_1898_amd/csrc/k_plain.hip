@@ -678,10 +678,7 @@ hipError_t launch_generate(int kind, uint32_t p, uint32_t* st, uint64_t n, uint6
     case MT19937: {
       const dim3 grid((unsigned)((n + 1) / 2)), block(256);
       const uint32_t d = (uint32_t)draws;
-      // Long launches are bound by their stores and gain from few rows being
-      // written at a time, a workgroup's each (65536 x 16384 f32 969 us, one
-      // row per wavefront 1016 us); all others run one stream per wavefront.
-      if (dtype != F64 && (n < 32768 || draws < 4096)) {
+      if (dtype != F64 && mt_row_per_wave(n, draws)) {
         const dim3 gw((unsigned)((n + 3) / 4));
         if (dtype == U32)
           hipLaunchKernelGGL((k_mt_wave<U32>), gw, block, 0, s, st, n, d, out, row_elems, off);

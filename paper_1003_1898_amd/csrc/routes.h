@@ -91,4 +91,26 @@ inline Cut xor128_cut(uint64_t n, uint64_t d, bool shared) {
   return {S, (d + S - 1) / S};  // (K - 1) S < d: no segment is empty
 }
 
+// --------------------------------------------------------------- MT19937 rows
+// 4-byte rows by one wavefront per stream, cached, or by a workgroup, past the
+// cache.  The workgroup's take more instructions but write fewer rows at a time,
+// which pays once states and rows no longer fit the 256 MB last-level cache
+// together.  f32, wavefront and workgroup: 65536 x 400 (270 MB) 71 and 83 us,
+// x 500 (296 MB) 108 and 88, x 4096 359 and 249; 40000 x 1000 (260 MB) 58 and 68,
+// x 1500 (340 MB) 112 and 86; 20011 x 3072 (296 MB) 59 and 67, x 4096 98 and 86;
+// 15040 x 12576 176 and 159.  Rows that start at uneven places cost the workgroup
+// some of that (27360 x 2125, 301 MB, 62 and 88 us; 28083 x 8075 261 and 279).
+// States beyond the cache by themselves leave nothing to lose (131072 x 800 247
+// and 280, x 2000 406 and 382; 96000 x 64 112 and 96).
+constexpr uint64_t kMtStateBytes = 2512;
+inline bool mt_row_per_wave(uint64_t n, uint64_t draws) {
+  const bool even = draws % 4 == 0;
+  if (n <= 14000) return true;
+  if (n >= 110000) return draws <= 1500;
+  if (draws >= (even ? 8192u : 6500u)) return !even && n < 32768;
+  if (n <= 18000) return true;
+  const uint64_t bytes = n * (kMtStateBytes + 4 * draws);
+  return bytes <= (n <= 22528 ? 300'000'000u : n > 80000 ? 264'500'000u : even || n > 40000 ? 280'000'000u : 305'000'000u);
+}
+
 }  // namespace prng

@@ -15,6 +15,8 @@ int main() {
     } else if (rule == "lux" || rule == "lux_shared") {
       const prng::Cut c = prng::lux_cut(n, d, (uint32_t)x, rule == "lux_shared");
       printf("%llu %llu\n", (unsigned long long)c.S, (unsigned long long)c.K);
+    } else if (rule == "mt19937") {
+      printf("%d\n", (int)prng::mt_row_per_wave(n, d));
     } else {
       return 1;
     }

@@ -37,3 +37,9 @@ def test_xor128_rows(oracle, n, calls):
                                        (32800, 223, ((500, "f32"), (390, "u32"), (120, "f64")))])
 def test_ranlux_rows(oracle, n, p, calls):
     _check_rows(oracle, "ranlux", n, calls, p)
+
+
+@pytest.mark.parametrize("n,calls", [(40001, ((1001, "f32"), (1249, "u32"))), (24003, ((2100, "f32_paper"),)),
+                                     (18002, ((3500, "u32"),))])
+def test_mt_rows(oracle, n, calls):
+    _check_rows(oracle, "mt19937", n, calls)

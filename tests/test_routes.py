@@ -80,3 +80,13 @@ def test_ranlux_cuts_are_whole(routes, rule):
         assert (K - 1) * S < d <= K * S and 1 <= K <= 64, (n, d, p)
         assert K == 1 or (S % 96 == 0 and K * ((n + 255) // 256) < 1 << 24), (n, d, p)
         assert rule == "lux" or K == 1 or d >= 3072, (n, d)
+
+
+# --------------------------------------------------------------- MT19937 rows
+@pytest.mark.parametrize("n,d,wave", [(256, 16384, 1), (14000, 16384, 1), (18000, 4096, 1), (19968, 8256, 0),
+                                      (20011, 3072, 1), (24000, 3000, 0), (23516, 2503, 1), (28083, 8075, 1),
+                                      (32768, 1248, 1), (40000, 1500, 0), (49152, 800, 0), (65536, 400, 1),
+                                      (65536, 500, 0), (65536, 16384, 0), (96000, 64, 0), (131072, 800, 1),
+                                      (131072, 2000, 0)])
+def test_mt_rows(routes, n, d, wave):
+    assert routes("mt19937", [(n, d, 0)]) == [[wave]]
