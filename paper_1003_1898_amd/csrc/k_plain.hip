@@ -644,17 +644,6 @@ hipError_t launch_lane_gen(int dtype, uint32_t p, uint32_t* st, uint64_t n, uint
   return hipGetLastError();
 }
 
-// RANMAR runs one stream per lane when the lanes keep at least three quarters
-// of the 1024 SIMDs busy (one wavefront each; its window takes most of the
-// registers), one per wavefront otherwise.  A lane's time does not fall with
-// the stream count: f32, per lane and per wavefront, 65536 x 4096 182 and 260
-// us (the lanes' rows are stored in longer runs), 65536 x 1024 57 and 67 us,
-// 16384 x 4096 155 and 48 us, 4096 x 1000 55 and 8.3 us.
-bool lanes_fill(uint64_t n) {
-  const uint64_t waves = (n + 63) / 64, rounds = (waves + 1023) / 1024;
-  return 4 * waves >= 3 * 1024 * rounds;
-}
-
 }  // namespace
 
 hipError_t launch_generate(int kind, uint32_t p, uint32_t* st, uint64_t n, uint64_t draws, int dtype, void* out,
@@ -667,7 +656,7 @@ hipError_t launch_generate(int kind, uint32_t p, uint32_t* st, uint64_t n, uint6
     case RANECU:
       return launch_leap<LeapRanecu>(dtype, st, n, draws, out, row_elems, off, s);
     case RANMAR:
-      if (lanes_fill(n)) return launch_lane_gen<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      if (ranmar_row_per_lane(n, draws)) return launch_lane_gen<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
       return launch_ranmar(dtype, st, n, draws, out, row_elems, off, s);
     case DRAND48:
       return launch_leap<LeapLcg48<25214903917ull, 11u>>(dtype, st, n, draws, out, row_elems, off, s);

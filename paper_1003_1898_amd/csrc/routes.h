@@ -113,4 +113,22 @@ inline bool mt_row_per_wave(uint64_t n, uint64_t draws) {
   return bytes <= (n <= 22528 ? 300'000'000u : n > 80000 ? 264'500'000u : even || n > 40000 ? 280'000'000u : 305'000'000u);
 }
 
+// --------------------------------------------------------------------- RANMAR
+// One lane per stream keeps at least three quarters of the 1024 SIMDs busy (one
+// wavefront each; its window takes most of the registers).
+inline bool lanes_fill(uint64_t n) {
+  const uint64_t waves = (n + 63) / 64, rounds = (waves + 1023) / 1024;
+  return 4 * waves >= 3 * 1024 * rounds;
+}
+
+// Rows by one lane per stream or by one wavefront.  A lane's time does not fall
+// with the stream count; it stores its rows in longer runs, which shows in long
+// launches, and a call of one whole 128-draw chunk has no ragged rows.  f32, lane
+// and wavefront: 65536 x 4096 176 and 255 us, 44000 x 4096 157 and 172, 40000 x
+// 4096 154 and 157, 40000 x 128 12 and 16, 28000 x 128 12 and 12; 40000 x 1000 55
+// and 32, 16384 x 4096 155 and 48, 4096 x 1000 50 and 8.
+inline bool ranmar_row_per_lane(uint64_t n, uint64_t draws) {
+  return lanes_fill(n) || (n >= 28672 && draws == 128) || (n >= 43008 && n < 49152 && draws >= 4096);
+}
+
 }  // namespace prng

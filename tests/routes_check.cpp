@@ -17,6 +17,8 @@ int main() {
       printf("%llu %llu\n", (unsigned long long)c.S, (unsigned long long)c.K);
     } else if (rule == "mt19937") {
       printf("%d\n", (int)prng::mt_row_per_wave(n, d));
+    } else if (rule == "ranmar") {
+      printf("%d\n", (int)prng::ranmar_row_per_lane(n, d));
     } else {
       return 1;
     }

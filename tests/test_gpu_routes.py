@@ -43,3 +43,9 @@ def test_ranlux_rows(oracle, n, p, calls):
                                      (18002, ((3500, "u32"),))])
 def test_mt_rows(oracle, n, calls):
     _check_rows(oracle, "mt19937", n, calls)
+
+
+@pytest.mark.parametrize("n,calls", [(28675, ((128, "f32"), (64, "f64"), (128, "u32"), (127, "f32"))),
+                                     (43009, ((4097, "u32"), (2049, "f64")))])
+def test_ranmar_rows(oracle, n, calls):
+    _check_rows(oracle, "ranmar", n, calls)

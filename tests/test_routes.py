@@ -90,3 +90,11 @@ def test_ranlux_cuts_are_whole(routes, rule):
                                       (131072, 2000, 0)])
 def test_mt_rows(routes, n, d, wave):
     assert routes("mt19937", [(n, d, 0)]) == [[wave]]
+
+
+# --------------------------------------------------------------------- RANMAR
+@pytest.mark.parametrize("n,d,lane", [(40000, 128, 1), (16384, 128, 0), (40000, 256, 0), (44000, 4096, 1),
+                                      (40000, 4096, 0), (49152, 1, 1), (65536, 16384, 1), (66048, 4096, 0),
+                                      (81920, 128, 1), (81920, 2048, 0)])
+def test_ranmar_rows(routes, n, d, lane):
+    assert routes("ranmar", [(n, d, 0)]) == [[lane]]
