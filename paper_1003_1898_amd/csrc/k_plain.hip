@@ -750,7 +750,7 @@ hipError_t launch_generate_packed(int kind, uint32_t p, uint32_t* st, uint64_t n
     case RANECU:
       return launch_leap_pack<Ranecu<>>(dtype, st, n, draws, out, row_elems, off, s);
     case RANMAR:
-      if (lanes_fill(n)) return launch_lane_pack<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      if (ranmar_packed_per_lane(n, draws)) return launch_lane_pack<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
       return launch_ranmar_packed(dtype, st, n, draws, out, row_elems, off, s);
     case RANLUX:
       return launch_lane_pack<Ranlux<96>>(dtype, p, st, n, draws, out, row_elems, off, s);

@@ -131,4 +131,19 @@ inline bool ranmar_row_per_lane(uint64_t n, uint64_t draws) {
   return lanes_fill(n) || (n >= 28672 && draws == 128) || (n >= 43008 && n < 49152 && draws >= 4096);
 }
 
+// Interleaved rows by one lane per stream or by four wavefronts on a row's four
+// streams, from the times of both in us.  A lane's chunks of 128 draws go out
+// whole only where every wavefront is full; ragged ends cost it 14 us.  Lane and
+// wavefronts: 40000 x 1 19 and 27 us, x 128 12 and 30, x 256 18 and 31, x 512 27
+// and 34, x 1000 61 and 40; 24000 x 256 16 and 21, x 512 25 and 23; 16384 x 100 27
+// and 15; 81920 x 384 44 and 67; 48000 x 2048 83 and 95.
+inline bool ranmar_packed_per_lane(uint64_t n, uint64_t draws) {
+  if (lanes_fill(n)) return true;
+  if (n >= 45056 && n < 49152 && n % 64 == 0 && draws % 128 == 0 && draws >= 2048) return true;
+  const double rounds = (double)((n + 65535) / 65536), d = (double)draws, chunks = (double)((draws + 127) / 128);
+  const double whole = 7.0 + 4.9 * chunks + (draws % 128 ? 14.0 : 0.0) + (n % 64 ? 0.014 * d : 0.0);
+  const double lane = rounds * (draws < 128 ? 18.0 + 0.07 * d : whole);
+  return lane < 4.0 + (double)n * (62e-5 + 3e-7 * d);
+}
+
 }  // namespace prng

@@ -19,6 +19,8 @@ int main() {
       printf("%d\n", (int)prng::mt_row_per_wave(n, d));
     } else if (rule == "ranmar") {
       printf("%d\n", (int)prng::ranmar_row_per_lane(n, d));
+    } else if (rule == "ranmar_packed") {
+      printf("%d\n", (int)prng::ranmar_packed_per_lane(n, d));
     } else {
       return 1;
     }

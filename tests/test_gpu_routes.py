@@ -49,3 +49,20 @@ def test_mt_rows(oracle, n, calls):
                                      (43009, ((4097, "u32"), (2049, "f64")))])
 def test_ranmar_rows(oracle, n, calls):
     _check_rows(oracle, "ranmar", n, calls)
+
+
+def _check_packed(oracle, kind, n, calls):
+    print(f"\n[routes packed] {kind} n={n}", flush=True)
+    seeds = inputs.seed_words(kind, 78, n)
+    g = Generator(kind, n, seed_words=seeds)
+    st = oracle.init(kind, seeds)
+    for count, dt in calls:
+        got = g.generate_packed4(count, dt).cpu().numpy().transpose(0, 2, 1).reshape(n, count)
+        assert np.array_equal(bits(got), bits(oracle.generate(kind, st, count, dt, threads=8))), f"{count} {dt}"
+        assert np.array_equal(g.state_words(), st), f"state after {count} {dt}"
+
+
+@pytest.mark.parametrize("n,calls", [(40000, ((1, "f32"), (128, "u32"), (257, "f32_paper"), (900, "f32"), (256, "u32"))),
+                                     (24004, ((128, "f32_paper"), (384, "f32"), (1, "u32")))])
+def test_ranmar_interleaved_rows(oracle, n, calls):
+    _check_packed(oracle, "ranmar", n, calls)

@@ -98,3 +98,10 @@ def test_mt_rows(routes, n, d, wave):
                                       (81920, 128, 1), (81920, 2048, 0)])
 def test_ranmar_rows(routes, n, d, lane):
     assert routes("ranmar", [(n, d, 0)]) == [[lane]]
+
+
+@pytest.mark.parametrize("n,d,lane", [(40000, 1, 1), (40000, 256, 1), (40000, 512, 1), (40000, 1000, 0),
+                                      (24000, 128, 1), (24000, 512, 0), (16384, 100, 0), (4096, 128, 0),
+                                      (81920, 384, 1), (66048, 1000, 0), (48000, 2048, 1), (131072, 1, 1)])
+def test_ranmar_interleaved_rows(routes, n, d, lane):
+    assert routes("ranmar_packed", [(n, d, 0)]) == [[lane]]
