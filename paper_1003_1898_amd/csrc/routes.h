@@ -146,4 +146,13 @@ inline bool ranmar_packed_per_lane(uint64_t n, uint64_t draws) {
   return lane < 4.0 + (double)n * (62e-5 + 3e-7 * d);
 }
 
+// Consumer by one lane per stream or by one wavefront, which pays for its window
+// and histogram with every stream.  Lane and wavefront: 20011 x 16 23 and 28 us,
+// x 256 24 and 30, x 512 33 and 31; 32768 x 512 34 and 45, x 1000 56 and 52; 16384 x
+// 16 22 and 21; 40000 x 16 33 to 50 and 45 (a lane's times depend on where the
+// histograms lie in memory), 81920 x 16 99 and 88.
+inline bool ranmar_consumer_per_lane(uint64_t n, uint64_t draws) {
+  return n >= 17000 && n <= 36000 && draws <= (n >= 24000 ? 512u : 256u);
+}
+
 }  // namespace prng

@@ -21,6 +21,8 @@ int main() {
       printf("%d\n", (int)prng::ranmar_row_per_lane(n, d));
     } else if (rule == "ranmar_packed") {
       printf("%d\n", (int)prng::ranmar_packed_per_lane(n, d));
+    } else if (rule == "ranmar_consumer") {
+      printf("%d\n", (int)prng::ranmar_consumer_per_lane(n, d));
     } else {
       return 1;
     }

@@ -66,3 +66,21 @@ def _check_packed(oracle, kind, n, calls):
                                      (24004, ((128, "f32_paper"), (384, "f32"), (1, "u32")))])
 def test_ranmar_interleaved_rows(oracle, n, calls):
     _check_packed(oracle, "ranmar", n, calls)
+
+
+def _check_consumer(oracle, kind, n, calls):
+    print(f"\n[routes consumer] {kind} n={n}", flush=True)
+    seeds = inputs.seed_words(kind, 79, n)
+    g = Generator(kind, n, seed_words=seeds)
+    st = oracle.init(kind, seeds)
+    for draws in calls:
+        s, h = g.fused_sum_hist(draws)
+        rs, rh = oracle.fused(kind, st, draws, threads=8)
+        assert np.array_equal(s.cpu().numpy(), rs), f"draws {draws}"
+        assert np.array_equal(h.cpu().numpy(), rh), f"draws {draws}"
+        assert np.array_equal(g.state_words(), st), f"draws {draws}"
+
+
+@pytest.mark.parametrize("n,calls", [(17001, (1, 128, 255, 257)), (24001, (0, 130, 512, 513))])
+def test_ranmar_consumer(oracle, n, calls):
+    _check_consumer(oracle, "ranmar", n, calls)

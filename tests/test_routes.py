@@ -105,3 +105,9 @@ def test_ranmar_rows(routes, n, d, lane):
                                       (81920, 384, 1), (66048, 1000, 0), (48000, 2048, 1), (131072, 1, 1)])
 def test_ranmar_interleaved_rows(routes, n, d, lane):
     assert routes("ranmar_packed", [(n, d, 0)]) == [[lane]]
+
+
+@pytest.mark.parametrize("n,d,lane", [(20011, 16, 1), (20011, 512, 0), (32768, 512, 1), (32768, 1000, 0),
+                                      (16384, 16, 0), (4096, 1 << 20, 0), (40000, 16, 0)])
+def test_ranmar_consumer(routes, n, d, lane):
+    assert routes("ranmar_consumer", [(n, d, 0)]) == [[lane]]
