@@ -610,7 +610,8 @@ hipError_t launch_lane_pack(int dtype, uint32_t p, uint32_t* st, uint64_t n, uin
 template <class G>
 hipError_t launch_leap_pack(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
                             uint64_t off, hipStream_t s) {
-  if (n > kWaveStreams) return launch_lane_pack<G>(dtype, 0u, st, n, draws, out, row_elems, off, s);
+  if (n > kWaveStreams || leap_packed_per_lane(std::is_same_v<G, Ranecu<>>, n, draws))
+    return launch_lane_pack<G>(dtype, 0u, st, n, draws, out, row_elems, off, s);
   const uint64_t want = std::min((4096 + n / 4 - 1) / (n / 4), (draws + 63) / 64);
   if (want >= 16) return launch_leap_pack_w<G, 16>(dtype, st, n, draws, out, row_elems, off, s);
   if (want >= 4) return launch_leap_pack_w<G, 4>(dtype, st, n, draws, out, row_elems, off, s);

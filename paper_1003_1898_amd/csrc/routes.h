@@ -155,4 +155,20 @@ inline bool ranmar_consumer_per_lane(uint64_t n, uint64_t draws) {
   return n >= 17000 && n <= 36000 && draws <= (n >= 24000 ? 512u : 256u);
 }
 
+// ------------------------------------------ interleaved rows of the leap kinds
+// GGL, RANECU, DRAND48 and RANNYU leap along a row of four streams, after up to
+// ten products per stream that bring a lane to its place: RANECU, whose states
+// are two, keeps one lane per stream where few whole 128-draw chunks of full
+// wavefronts are cheaper (times in us), the others for one chunk.  Lane and leap:
+// RANECU 65536 x 128 12 and 22, x 256 20 and 27, x 512 33 and 38, x 1024 70 and 60,
+// 40000 x 256 18 and 19, x 384 24 and 23; GGL 65536 x 128 10 and 12, x 256 15 and
+// 14, 32768 x 128 8 and 8, 44000 x 128 (a wavefront not full) 10 and 9.
+inline bool leap_packed_per_lane(bool ranecu, uint64_t n, uint64_t draws) {
+  if (draws % 128) return false;
+  if (!ranecu) return draws == 128 && (n % 64 ? n >= 56000 && n <= 65536 : n >= 38000);
+  if (n % 64) return false;
+  const double rounds = (double)((n + 65535) / 65536), d = (double)draws;
+  return draws <= 768 && rounds * (4.7 + 0.051 * d) < 1.5 + (double)n * (30e-5 + 6.5e-7 * d);
+}
+
 }  // namespace prng

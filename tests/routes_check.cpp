@@ -23,6 +23,8 @@ int main() {
       printf("%d\n", (int)prng::ranmar_packed_per_lane(n, d));
     } else if (rule == "ranmar_consumer") {
       printf("%d\n", (int)prng::ranmar_consumer_per_lane(n, d));
+    } else if (rule == "leap_packed") {
+      printf("%d\n", (int)prng::leap_packed_per_lane(x != 0, n, d));
     } else {
       return 1;
     }

@@ -84,3 +84,9 @@ def _check_consumer(oracle, kind, n, calls):
 @pytest.mark.parametrize("n,calls", [(17001, (1, 128, 255, 257)), (24001, (0, 130, 512, 513))])
 def test_ranmar_consumer(oracle, n, calls):
     _check_consumer(oracle, "ranmar", n, calls)
+
+
+@pytest.mark.parametrize("kind", ["ggl", "ranecu", "drand48", "rannyu"])
+def test_leap_interleaved_rows(oracle, kind):
+    paper = "f32_paper" if kind in ("ggl", "ranecu") else "u32"
+    _check_packed(oracle, kind, 57344, ((128, "u32"), (128, paper), (256, "f32"), (129, "f32"), (128, "f32")))

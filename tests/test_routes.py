@@ -111,3 +111,12 @@ def test_ranmar_interleaved_rows(routes, n, d, lane):
                                       (16384, 16, 0), (4096, 1 << 20, 0), (40000, 16, 0)])
 def test_ranmar_consumer(routes, n, d, lane):
     assert routes("ranmar_consumer", [(n, d, 0)]) == [[lane]]
+
+
+# ------------------------------------------ interleaved rows of the leap kinds
+@pytest.mark.parametrize("n,d,ranecu,lane", [(65536, 128, 1, 1), (65536, 256, 1, 1), (65536, 512, 1, 1),
+                                             (65536, 1024, 1, 0), (40000, 384, 1, 0), (16384, 256, 1, 0),
+                                             (65536, 250, 1, 0), (65536, 128, 0, 1), (65536, 256, 0, 0),
+                                             (16384, 128, 0, 0)])
+def test_leap_interleaved_rows(routes, n, d, ranecu, lane):
+    assert routes("leap_packed", [(n, d, ranecu)]) == [[lane]]
