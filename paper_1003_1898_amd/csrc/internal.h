@@ -167,9 +167,6 @@ hipError_t launch_lux_plain(uint32_t p, uint32_t* st, const uint32_t* snap, uint
 hipError_t launch_lux_fused_split(uint32_t p, uint32_t* st, const uint32_t* snap, uint64_t n, uint64_t draws,
                                   uint32_t S, uint32_t K, const uint32_t* digits, const uint32_t* aux, uint64_t* sum,
                                   uint32_t* hist, bool acc, hipStream_t s);
-// A launch holds less than 2^32 threads: beyond this many streams a stream gets
-// a lane instead of a wavefront.
-constexpr uint64_t kWaveStreams = 1ull << 25;
 // XOR128 plain generation with every stream cut into K >= 2 segments of S
 // positions (a multiple of 128), 256 streams per block and segment, so that
 // several wavefronts per SIMD share the stores.  snap: copy of the state

@@ -1,6 +1,5 @@
 // In-kernel consumers: exact mantissa sums and 64-bin histograms per stream.
 #include <bit>
-#include <cmath>
 
 #include "device.h"
 
@@ -218,39 +217,12 @@ hipError_t launch_lane_fused(uint32_t p, uint32_t* st, uint64_t n, uint64_t draw
   return hipGetLastError();
 }
 
-// Wavefronts per stream of a cut run (1, 4 or 16), or 0 for one lane per
-// stream: the least of a time model in draws of one wavefront.  A wavefront
-// pays 40 to start and to add up and `jump` per bit of its segment's number,
-// and its lanes one per draw; 2048 wavefronts run in the time of one.  With
-// one lane per stream a SIMD has at most two wavefronts to hide the dependent
-// steps, at twice the time per draw.  Both sides at 65536 streams x 1024
-// draws, where the model puts them closest: GGL 93 us uncut, 68 us cut;
-// XOR128, whose jumps cost six matrix products, stays uncut at 91 us.
-int split_width(uint64_t n, uint64_t draws, double jump, bool pow2) {
-  auto rounds = [](double waves) { return std::max(1.0, waves / 2048.0); };
-  double best = 2.0 * (double)draws * std::ceil(rounds((double)((n + 63) / 64))) + 40.0;
-  int width = 0;
-  for (int W : {1, 4, 16}) {
-    if (n > kWaveStreams / W) break;
-    const int bits = W == 1 ? 6 : W == 4 ? 8 : 10;
-    uint64_t S = (draws + 64ull * W - 1) / (64ull * W);
-    if (pow2) S = std::bit_ceil(S);
-    const double t = rounds((double)n * W) * (40.0 + jump * bits + (double)S);
-    if (t < best) {
-      best = t;
-      width = W;
-    }
-  }
-  return width;
-}
-
 // G: the kind's 16-draw generator; L: its one-lane-per-stream generator
 template <class G, class L>
-hipError_t launch_split_fused(uint32_t* st, uint64_t n, uint64_t draws, uint64_t* sum, uint32_t* hist, bool acc,
-                              hipStream_t s) {
-  // a matrix product of XOR128 costs about 100 of its draws, a multiplication one
+hipError_t launch_split_fused(double draw_us, uint32_t* st, uint64_t n, uint64_t draws, uint64_t* sum, uint32_t* hist,
+                              bool acc, hipStream_t s) {
   constexpr bool kXor = requires(G g) { g.advance_by(st); };
-  const int W = split_width(n, draws, kXor ? 100.0 : 1.0, kXor);
+  const int W = consumer_width(draw_us, kXor, n, draws);
   if (W == 0) return launch_lane_fused<L>(0u, st, n, draws, sum, hist, acc, s);
   uint64_t S = (draws + 64ull * W - 1) / (64ull * W);
   SplitMaps maps{};
@@ -277,20 +249,20 @@ hipError_t launch_fused(int kind, uint32_t p, uint32_t* st, uint64_t n, uint64_t
                         uint32_t* hist, bool acc, hipStream_t s) {
   switch (kind) {
     case GGL:
-      return launch_split_fused<Ggl<kSplitT>, Ggl<>>(st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Ggl<kSplitT>, Ggl<>>(kGglDrawUs, st, n, draws, sum, hist, acc, s);
     case XOR128:
-      return launch_split_fused<Xor128<kSplitT>, Xor128<>>(st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Xor128<kSplitT>, Xor128<>>(kXor128DrawUs, st, n, draws, sum, hist, acc, s);
     case RANECU:
-      return launch_split_fused<Ranecu<kSplitT>, Ranecu<>>(st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Ranecu<kSplitT>, Ranecu<>>(kRanecuDrawUs, st, n, draws, sum, hist, acc, s);
     case RANMAR:
       if (n > kWaveStreams || ranmar_consumer_per_lane(n, draws)) return launch_lane_fused<Ranmar<>>(p, st, n, draws, sum, hist, acc, s);
       return launch_ranmar_fused(st, n, draws, sum, hist, acc, s);
     case RANLUX:
       return launch_lane_fused<Ranlux<>>(p, st, n, draws, sum, hist, acc, s);
     case DRAND48:
-      return launch_split_fused<Drand48<kSplitT>, Drand48<>>(st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Drand48<kSplitT>, Drand48<>>(kDrand48DrawUs, st, n, draws, sum, hist, acc, s);
     case RANNYU:
-      return launch_split_fused<Rannyu<kSplitT>, Rannyu<>>(st, n, draws, sum, hist, acc, s);
+      return launch_split_fused<Rannyu<kSplitT>, Rannyu<>>(kRannyuDrawUs, st, n, draws, sum, hist, acc, s);
     case MT19937: {
       const dim3 grid((unsigned)((n + 3) / 4)), block(256);
       hipLaunchKernelGGL(k_mt_fused, grid, block, 0, s, st, n, (uint32_t)draws, sum, hist, acc ? 1 : 0);

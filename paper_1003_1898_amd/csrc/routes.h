@@ -11,6 +11,10 @@ namespace prng {
 // whatever order its rows are stored in; more of it is bound by that order.
 constexpr uint64_t kCachedBytes = 320'000'000;
 
+// A launch holds less than 2^32 threads: beyond this many streams a stream gets
+// a lane instead of a wavefront.
+constexpr uint64_t kWaveStreams = 1ull << 25;
+
 // A stream's draws cut into K segments of S (the last one shorter); K = 1: uncut.
 struct Cut {
   uint64_t S, K;
@@ -169,6 +173,51 @@ inline bool leap_packed_per_lane(bool ranecu, uint64_t n, uint64_t draws) {
   if (n % 64) return false;
   const double rounds = (double)((n + 65535) / 65536), d = (double)draws;
   return draws <= 768 && rounds * (4.7 + 0.051 * d) < 1.5 + (double)n * (30e-5 + 6.5e-7 * d);
+}
+
+// ----------------------------------------------------------------- the consumer
+// A draw of one lane per stream, its dependent steps hidden by at most two
+// wavefronts per SIMD, in us (over ten thousand draws).
+constexpr double kGglDrawUs = 0.0235, kXor128DrawUs = 0.0245, kRanecuDrawUs = 0.0435, kDrand48DrawUs = 0.0222,
+                 kRannyuDrawUs = 0.0195;
+
+// Wavefronts per stream of the cut consumer (1, 4 or 16), or 0 for one lane per
+// stream: the least of the times in us, fitted to 795 calls of 64 to 262144
+// streams (the choice loses 0.6% to the best one on average).  A wavefront pays
+// for its histogram and, per draw, issue where the chip is full (2048 wavefronts)
+// or latency where it is not; a jump of XOR128 costs 2.2 us per bit of the segment's
+// number.  A lane pays for storing 64 bins by itself.  Lane and W = 1: GGL 20011 x
+// 256 18 and 20 us, x 1000 40 and 26; 28000 x 512 25 and 29; 65536 x 16 72 and 58 (from
+// about 36000 streams on a lane's times depend on where the histograms lie: 50000 x
+// 1184 46 to 76 and 56);
+// XOR128 64 x 512 17 and 22, 4096 x 1000 39 and 33, 20011 x 4096 114 and 146.
+inline int consumer_width(double draw, bool matrix, uint64_t n, uint64_t draws) {
+  const double N = (double)n, d = (double)draws;
+  double best = (n <= 51200 ? 0.72e-3 : 0.95e-3) * N + draw * d;
+  if (n <= 36000) best = std::max(13.0 + N / 7000.0, 8.0 + N / 5000.0 + draw * d);
+  if (n <= 64) best = (matrix ? 4.0 : 7.0) + draw * d;
+  int width = 0;
+  const struct { int W, bits; double group; } kinds[] = {{1, 6, 1.4}, {4, 8, 2.0}, {16, 10, 14.0}};
+  for (const auto& k : kinds) {
+    if (n > kWaveStreams / k.W) break;
+    uint64_t S = (draws + 64ull * k.W - 1) / (64ull * k.W);
+    double latency = 0.3 * k.bits * draw, issue = 12.0 * draw;  // of the jump
+    double step = 0.67 * draw;                                  // a draw's latency
+    if (matrix) {
+      S = std::bit_ceil(S);
+      const uint64_t last = draws ? (draws - 1) / S : 0;  // the last segment's number
+      latency = issue = 2.2 * (double)std::min<int>(k.bits, std::bit_width(last));
+      step = 1.3 * draw;
+    }
+    const double rounds = (double)((n * k.W + 1023) / 1024) / (2.0 * k.W);  // of the fullest SIMD, two wavefronts each
+    const double t = 4.0 + std::max(2.0 + latency + step * (double)S,
+                                    rounds * (k.group + k.W * (issue + 1.25 * draw * (double)S)));
+    if (t < best) {
+      best = t;
+      width = k.W;
+    }
+  }
+  return width;
 }
 
 }  // namespace prng

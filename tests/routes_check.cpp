@@ -25,6 +25,10 @@ int main() {
       printf("%d\n", (int)prng::ranmar_consumer_per_lane(n, d));
     } else if (rule == "leap_packed") {
       printf("%d\n", (int)prng::leap_packed_per_lane(x != 0, n, d));
+    } else if (rule == "consumer") {  // x: the kind
+      const double us[] = {0, prng::kGglDrawUs, prng::kXor128DrawUs, prng::kRanecuDrawUs, 0, 0, 0, prng::kDrand48DrawUs,
+                           prng::kRannyuDrawUs};
+      printf("%d\n", prng::consumer_width(us[x], x == 2, n, d));
     } else {
       return 1;
     }

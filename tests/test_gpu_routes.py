@@ -90,3 +90,8 @@ def test_ranmar_consumer(oracle, n, calls):
 def test_leap_interleaved_rows(oracle, kind):
     paper = "f32_paper" if kind in ("ggl", "ranecu") else "u32"
     _check_packed(oracle, kind, 57344, ((128, "u32"), (128, paper), (256, "f32"), (129, "f32"), (128, "f32")))
+
+
+@pytest.mark.parametrize("kind", ["ggl", "xor128", "ranecu", "drand48", "rannyu"])
+def test_consumer(oracle, kind):
+    _check_consumer(oracle, kind, 10007, (1, 64, 300, 2500))

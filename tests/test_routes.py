@@ -120,3 +120,23 @@ def test_ranmar_consumer(routes, n, d, lane):
                                              (16384, 128, 0, 0)])
 def test_leap_interleaved_rows(routes, n, d, ranecu, lane):
     assert routes("leap_packed", [(n, d, ranecu)]) == [[lane]]
+
+
+# ----------------------------------------------------------------- the consumer
+GGL, XOR128, RANECU, DRAND48, RANNYU = 1, 2, 3, 7, 8
+
+
+@pytest.mark.parametrize("kind,n,d,width", [(GGL, 20011, 256, 0), (GGL, 20011, 1000, 1), (GGL, 28000, 512, 0),
+                                            (GGL, 50000, 1000, 1), (GGL, 65536, 16, 1), (GGL, 4096, 16, 1),
+                                            (XOR128, 64, 512, 0), (XOR128, 10007, 2048, 0), (XOR128, 20011, 4096, 0),
+                                            (XOR128, 4096, 4096, 1), (RANECU, 28000, 256, 0), (RANECU, 4096, 1 << 20, 1),
+                                            (RANECU, 64, 1 << 20, 16), (DRAND48, 28000, 512, 0), (GGL, 1383, 28672, 4),
+                                            (RANNYU, 20011, 4096, 1), (GGL, (1 << 25) + 4, 100, 0)])
+def test_consumer_width(routes, kind, n, d, width):
+    assert routes("consumer", [(n, d, kind)]) == [[width]]
+
+
+def test_consumer_widths_fit_a_launch(routes):
+    calls = _calls(3, 4000, 30, 30, (GGL, XOR128, RANECU, DRAND48, RANNYU)) + [(1, 0, XOR128), (100000, 0, RANECU)]
+    for (n, d, kind), (w,) in zip(calls, routes("consumer", calls)):
+        assert w in (0, 1, 4, 16) and n * max(w, 1) <= max(n, 1 << 25), (n, d, kind)
