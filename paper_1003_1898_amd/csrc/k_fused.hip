@@ -263,11 +263,12 @@ hipError_t launch_fused(int kind, uint32_t p, uint32_t* st, uint64_t n, uint64_t
       return launch_split_fused<Drand48<kSplitT>, Drand48<>>(kDrand48DrawUs, st, n, draws, sum, hist, acc, s);
     case RANNYU:
       return launch_split_fused<Rannyu<kSplitT>, Rannyu<>>(kRannyuDrawUs, st, n, draws, sum, hist, acc, s);
-    case MT19937: {
-      const dim3 grid((unsigned)((n + 3) / 4)), block(256);
-      hipLaunchKernelGGL(k_mt_fused, grid, block, 0, s, st, n, (uint32_t)draws, sum, hist, acc ? 1 : 0);
-      return hipGetLastError();
-    }
+    case MT19937:
+      return for_stream_ranges(n, kWaveStreams, [&](uint64_t s0, uint64_t m) {
+        hipLaunchKernelGGL(k_mt_fused, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, st + s0 * kMtStride, m,
+                           (uint32_t)draws, sum + s0, hist + 64 * s0, acc ? 1 : 0);
+        return hipGetLastError();
+      });
   }
   return hipErrorInvalidValue;
 }

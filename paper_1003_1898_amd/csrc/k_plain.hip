@@ -336,14 +336,16 @@ struct LeapLcg48 {
   }
 };
 
+// n streams from `state` on, whose rows lie sn words apart
 template <class L, int DT, bool QUADS>
-__global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ state, uint64_t n, uint32_t draws,
-                                                       void* __restrict__ out, uint64_t row_elems, uint64_t elem_off) {
+__global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ state, uint64_t sn, uint64_t n,
+                                                       uint32_t draws, void* __restrict__ out, uint64_t row_elems,
+                                                       uint64_t elem_off) {
   const int lane = threadIdx.x & 63;
   const uint64_t s = (uint64_t)blockIdx.x * 4u + (threadIdx.x >> 6);
   if (s >= n || draws == 0) return;  // whole wavefront
   L g;
-  g.load(state, n, s);
+  g.load(state, sn, s);
   g.start(lane);  // X of position 4 l
   constexpr uint64_t es = DT == F64 ? 8 : 4;
   // position v's element at byte row + 4 v (an fp64 element per pair of draws)
@@ -371,7 +373,7 @@ __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ st
         h.leap();
         g = h;
       } else if (last - v < kLeapQuad) {
-        g.store_at(last - v, state, n, s);
+        g.store_at(last - v, state, sn, s);
       }
     }
   }
@@ -386,16 +388,16 @@ __global__ __launch_bounds__(256) void k_leap_generate(uint32_t* __restrict__ st
 // wavefront reads the four states before the barrier; the wavefront of a
 // row's last position writes its new state after it.
 template <class L, int DT, bool QUADS>
-__global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ state, uint64_t n, uint32_t draws,
-                                                       uint32_t Q, uint64_t j0, uint64_t j1, void* __restrict__ out,
-                                                       uint64_t row_elems, uint64_t elem_off) {
+__global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ state, uint64_t sn, uint64_t n,
+                                                       uint32_t draws, uint32_t Q, uint64_t j0, uint64_t j1,
+                                                       void* __restrict__ out, uint64_t row_elems, uint64_t elem_off) {
   const int lane = threadIdx.x & 63;
   const uint32_t w = uni(threadIdx.x >> 6);
   const uint64_t s0 = (uint64_t)blockIdx.x * 4u;
   L g[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r)
-    if (s0 + r < n) g[r].load(state, n, s0 + r);
+    if (s0 + r < n) g[r].load(state, sn, s0 + r);
   __syncthreads();
   const uint32_t beg = w * Q, end = min(beg + Q, draws);
   if (beg >= end) return;  // whole wavefront, after the barrier
@@ -426,7 +428,7 @@ __global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ st
           q.leap();
           h = q;
         } else if (end == draws && last - v < kLeapQuad) {
-          h.store_at(last - v, state, n, s);
+          h.store_at(last - v, state, sn, s);
         }
       }
     }
@@ -434,8 +436,8 @@ __global__ __launch_bounds__(256) void k_leap_quarters(uint32_t* __restrict__ st
 }
 
 template <class L, bool QUADS>
-hipError_t launch_leap_rows(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
-                            uint64_t off, hipStream_t s) {
+hipError_t launch_leap_rows(int dtype, uint32_t* st, uint64_t sn, uint64_t n, uint64_t draws, void* out,
+                            uint64_t row_elems, uint64_t off, hipStream_t s) {
   const dim3 grid((unsigned)((n + 3) / 4)), block(256);
   const uint32_t d = (uint32_t)draws;
   // rows of at least four blocks per wavefront go by quarters
@@ -446,20 +448,20 @@ hipError_t launch_leap_rows(int dtype, uint32_t* st, uint64_t n, uint64_t draws,
     L::q_map(Q, j0, j1);
     switch (dtype) {
       case U32:
-        hipLaunchKernelGGL((k_leap_quarters<L, U32, QUADS>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems,
+        hipLaunchKernelGGL((k_leap_quarters<L, U32, QUADS>), grid, block, 0, s, st, sn, n, d, q, j0, j1, out, row_elems,
                            off);
         break;
       case F32:
-        hipLaunchKernelGGL((k_leap_quarters<L, F32, QUADS>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems,
+        hipLaunchKernelGGL((k_leap_quarters<L, F32, QUADS>), grid, block, 0, s, st, sn, n, d, q, j0, j1, out, row_elems,
                            off);
         break;
       case F64:
-        hipLaunchKernelGGL((k_leap_quarters<L, F64, QUADS>), grid, block, 0, s, st, n, d, q, j0, j1, out, row_elems,
+        hipLaunchKernelGGL((k_leap_quarters<L, F64, QUADS>), grid, block, 0, s, st, sn, n, d, q, j0, j1, out, row_elems,
                            off);
         break;
       case F32P:
         if constexpr (requires { L::paper_f32(0u); }) {
-          hipLaunchKernelGGL((k_leap_quarters<L, F32P, QUADS>), grid, block, 0, s, st, n, d, q, j0, j1, out,
+          hipLaunchKernelGGL((k_leap_quarters<L, F32P, QUADS>), grid, block, 0, s, st, sn, n, d, q, j0, j1, out,
                              row_elems, off);
           break;
         }
@@ -471,17 +473,17 @@ hipError_t launch_leap_rows(int dtype, uint32_t* st, uint64_t n, uint64_t draws,
   }
   switch (dtype) {
     case U32:
-      hipLaunchKernelGGL((k_leap_generate<L, U32, QUADS>), grid, block, 0, s, st, n, d, out, row_elems, off);
+      hipLaunchKernelGGL((k_leap_generate<L, U32, QUADS>), grid, block, 0, s, st, sn, n, d, out, row_elems, off);
       break;
     case F32:
-      hipLaunchKernelGGL((k_leap_generate<L, F32, QUADS>), grid, block, 0, s, st, n, d, out, row_elems, off);
+      hipLaunchKernelGGL((k_leap_generate<L, F32, QUADS>), grid, block, 0, s, st, sn, n, d, out, row_elems, off);
       break;
     case F64:
-      hipLaunchKernelGGL((k_leap_generate<L, F64, QUADS>), grid, block, 0, s, st, n, d, out, row_elems, off);
+      hipLaunchKernelGGL((k_leap_generate<L, F64, QUADS>), grid, block, 0, s, st, sn, n, d, out, row_elems, off);
       break;
     case F32P:
       if constexpr (requires { L::paper_f32(0u); }) {
-        hipLaunchKernelGGL((k_leap_generate<L, F32P, QUADS>), grid, block, 0, s, st, n, d, out, row_elems, off);
+        hipLaunchKernelGGL((k_leap_generate<L, F32P, QUADS>), grid, block, 0, s, st, sn, n, d, out, row_elems, off);
         break;
       }
       return hipErrorInvalidValue;
@@ -496,9 +498,12 @@ template <class L>
 hipError_t launch_leap(int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out, uint64_t row_elems,
                        uint64_t off, hipStream_t s) {
   const uint64_t es = elem_bytes(dtype);
-  if (((reinterpret_cast<uint64_t>(out) + off * es) | (n > 1 ? row_elems * es : 0)) % 16 == 0)
-    return launch_leap_rows<L, true>(dtype, st, n, draws, out, row_elems, off, s);
-  return launch_leap_rows<L, false>(dtype, st, n, draws, out, row_elems, off, s);
+  const bool quads = ((reinterpret_cast<uint64_t>(out) + off * es) | (n > 1 ? row_elems * es : 0)) % 16 == 0;
+  return for_stream_ranges(n, kWaveStreams, [&](uint64_t s0, uint64_t m) {
+    void* const o = static_cast<char*>(out) + s0 * row_elems * es;
+    return quads ? launch_leap_rows<L, true>(dtype, st + s0, n, m, draws, o, row_elems, off, s)
+                 : launch_leap_rows<L, false>(dtype, st + s0, n, m, draws, o, row_elems, off, s);
+  });
 }
 
 // Interleaved rows of the multiplicative and affine generators: W wavefronts
@@ -645,6 +650,41 @@ hipError_t launch_lane_gen(int dtype, uint32_t p, uint32_t* st, uint64_t n, uint
   return hipGetLastError();
 }
 
+// one stream per wavefront (4-byte dtypes) or per workgroup
+hipError_t launch_mt_rows(bool wave, int dtype, uint32_t* st, uint64_t n, uint64_t draws, void* out,
+                          uint64_t row_elems, uint64_t off, hipStream_t s) {
+  const dim3 gw((unsigned)((n + 3) / 4)), grid((unsigned)((n + 1) / 2)), block(256);
+  const uint32_t d = (uint32_t)draws;
+  if (wave) {
+    if (dtype == U32)
+      hipLaunchKernelGGL((k_mt_wave<U32>), gw, block, 0, s, st, n, d, out, row_elems, off);
+    else if (dtype == F32)
+      hipLaunchKernelGGL((k_mt_wave<F32>), gw, block, 0, s, st, n, d, out, row_elems, off);
+    else if (dtype == F32P)
+      hipLaunchKernelGGL((k_mt_wave<F32P>), gw, block, 0, s, st, n, d, out, row_elems, off);
+    else
+      return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
+  switch (dtype) {
+    case U32:
+      hipLaunchKernelGGL((k_mt_generate<U32>), grid, block, 0, s, st, n, d, out, row_elems, off);
+      break;
+    case F32:
+      hipLaunchKernelGGL((k_mt_generate<F32>), grid, block, 0, s, st, n, d, out, row_elems, off);
+      break;
+    case F64:
+      hipLaunchKernelGGL((k_mt_generate<F64>), grid, block, 0, s, st, n, d, out, row_elems, off);
+      break;
+    case F32P:
+      hipLaunchKernelGGL((k_mt_generate<F32P>), grid, block, 0, s, st, n, d, out, row_elems, off);
+      break;
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_generate(int kind, uint32_t p, uint32_t* st, uint64_t n, uint64_t draws, int dtype, void* out,
@@ -666,37 +706,11 @@ hipError_t launch_generate(int kind, uint32_t p, uint32_t* st, uint64_t n, uint6
     case RANLUX:  // prng_generate runs RANLUX through launch_lux_plain
       return hipErrorInvalidValue;
     case MT19937: {
-      const dim3 grid((unsigned)((n + 1) / 2)), block(256);
-      const uint32_t d = (uint32_t)draws;
-      if (dtype != F64 && mt_row_per_wave(n, draws)) {
-        const dim3 gw((unsigned)((n + 3) / 4));
-        if (dtype == U32)
-          hipLaunchKernelGGL((k_mt_wave<U32>), gw, block, 0, s, st, n, d, out, row_elems, off);
-        else if (dtype == F32)
-          hipLaunchKernelGGL((k_mt_wave<F32>), gw, block, 0, s, st, n, d, out, row_elems, off);
-        else if (dtype == F32P)
-          hipLaunchKernelGGL((k_mt_wave<F32P>), gw, block, 0, s, st, n, d, out, row_elems, off);
-        else
-          return hipErrorInvalidValue;
-        return hipGetLastError();
-      }
-      switch (dtype) {
-        case U32:
-          hipLaunchKernelGGL((k_mt_generate<U32>), grid, block, 0, s, st, n, d, out, row_elems, off);
-          break;
-        case F32:
-          hipLaunchKernelGGL((k_mt_generate<F32>), grid, block, 0, s, st, n, d, out, row_elems, off);
-          break;
-        case F64:
-          hipLaunchKernelGGL((k_mt_generate<F64>), grid, block, 0, s, st, n, d, out, row_elems, off);
-          break;
-        case F32P:
-          hipLaunchKernelGGL((k_mt_generate<F32P>), grid, block, 0, s, st, n, d, out, row_elems, off);
-          break;
-        default:
-          return hipErrorInvalidValue;
-      }
-      return hipGetLastError();
+      const bool wave = dtype != F64 && mt_row_per_wave(n, draws);
+      return for_stream_ranges(n, kWaveStreams / 2, [&](uint64_t s0, uint64_t m) {
+        return launch_mt_rows(wave, dtype, st + s0 * kMtStride, m, draws,
+                              static_cast<char*>(out) + s0 * row_elems * elem_bytes(dtype), row_elems, off, s);
+      });
     }
   }
   return hipErrorInvalidValue;

@@ -12,8 +12,18 @@ namespace prng {
 constexpr uint64_t kCachedBytes = 320'000'000;
 
 // A launch holds less than 2^32 threads: beyond this many streams a stream gets
-// a lane instead of a wavefront.
+// a lane instead of a wavefront, or the streams several launches.
 constexpr uint64_t kWaveStreams = 1ull << 25;
+
+// launch(first, count) over the streams 0 .. n - 1, at most `most` (a multiple
+// of four) at a time, up to the first failure; the last launch's result.
+template <class F>
+auto for_stream_ranges(uint64_t n, uint64_t most, F launch) {
+  uint64_t s0 = 0;
+  auto e = launch(s0, std::min(n, most));
+  for (s0 = most; s0 < n && e == decltype(e){}; s0 += most) e = launch(s0, std::min(n - s0, most));
+  return e;
+}
 
 // A stream's draws cut into K segments of S (the last one shorter); K = 1: uncut.
 struct Cut {

@@ -29,6 +29,12 @@ int main() {
       const double us[] = {0, prng::kGglDrawUs, prng::kXor128DrawUs, prng::kRanecuDrawUs, 0, 0, 0, prng::kDrand48DrawUs,
                            prng::kRannyuDrawUs};
       printf("%d\n", prng::consumer_width(us[x], x == 2, n, d));
+    } else if (rule == "ranges") {
+      prng::for_stream_ranges(n, d, [](uint64_t s0, uint64_t m) {
+        printf("%llu %llu ", (unsigned long long)s0, (unsigned long long)m);
+        return 0;
+      });
+      printf("\n");
     } else {
       return 1;
     }

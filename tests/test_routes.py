@@ -140,3 +140,11 @@ def test_consumer_widths_fit_a_launch(routes):
     calls = _calls(3, 4000, 30, 30, (GGL, XOR128, RANECU, DRAND48, RANNYU)) + [(1, 0, XOR128), (100000, 0, RANECU)]
     for (n, d, kind), (w,) in zip(calls, routes("consumer", calls)):
         assert w in (0, 1, 4, 16) and n * max(w, 1) <= max(n, 1 << 25), (n, d, kind)
+
+
+def test_stream_ranges_cover_every_stream_once(routes):
+    for n, most in ((1, 8), (8, 8), (9, 8), (64, 8), (67, 12), ((1 << 26) + 5, 1 << 25)):
+        (got,) = routes("ranges", [(n, most, 0)])
+        first, count = got[0::2], got[1::2]
+        assert first == list(range(0, n, most)) and sum(count) == n and max(count) <= most
+        assert all(a + c == b for a, c, b in zip(first, count, first[1:] + [n]))
