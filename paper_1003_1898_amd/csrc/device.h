@@ -314,8 +314,7 @@ struct Ggl {
   // the paper's scaling x / 2147483647.0 in fp32, where that constant is 2^31
   static __device__ float paper_f32(uint32_t u) { return (float)u * 0x1p-31f; }
   // state J draws ahead: x a^J, with jd[0] = a^J mod m
-  __device__ uint32_t load_jumped(const uint32_t* st, uint64_t, uint64_t si, const uint32_t* jd, const uint32_t*,
-                                  uint32_t*) {
+  __device__ uint32_t load_jumped(const uint32_t* st, uint64_t, uint64_t si, const uint32_t* jd, const uint32_t*) {
     x = mulmod_2p31<1u>(st[si], jd[0]);
     return 0;
   }
@@ -363,8 +362,7 @@ struct Xor128 {
   static __device__ float paper_f32(uint32_t u) { return (float)u * 0x1p-32f; }
   // state J steps ahead: the state's 128 bits times the GF(2) matrix T^J, whose
   // row i (jd[4i..4i+3]) is the image of state bit i (bit i % 32 of word i / 32)
-  __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd, const uint32_t*,
-                                  uint32_t*) {
+  __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd, const uint32_t*) {
     uint32_t s[4] = {st[si], st[sn + si], st[2 * sn + si], st[3 * sn + si]};
     matvec<8>(s, jd);
     x = s[0];
@@ -450,8 +448,7 @@ struct Ranecu {
   // the paper's scaling Z * 2^-31
   static __device__ float paper_f32(uint32_t u) { return (float)u * 0x1p-31f; }
   // state J steps ahead: s1 a1^J mod m1, s2 a2^J mod m2 (jd = {a1^J, a2^J})
-  __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd, const uint32_t*,
-                                  uint32_t*) {
+  __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd, const uint32_t*) {
     s1 = mulmod_2p31<85u>(st[si], jd[0]);
     s2 = mulmod_2p31<249u>(st[sn + si], jd[1]);
     return 0;
@@ -505,8 +502,7 @@ struct Lcg48 {
     st[sn + si] = x1 & 0xFFFFu;
   }
   // state J steps ahead: A_J X + C_J mod 2^48, jd = {A_J lo, hi, C_J lo, hi}
-  __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd, const uint32_t*,
-                                  uint32_t*) {
+  __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd, const uint32_t*) {
     const uint64_t x = (uint64_t)st[si] | ((uint64_t)st[sn + si] << 32);
     const uint64_t a = (uint64_t)jd[0] | ((uint64_t)jd[1] << 32), c = (uint64_t)jd[2] | ((uint64_t)jd[3] << 32);
     const uint64_t y = a * x + c;
@@ -563,6 +559,7 @@ struct SplitMaps {
 template <int TT = 128>
 struct Ranmar {
   static constexpr int T = TT, BITS = 24;
+  static constexpr bool kStoresInChunk = true;  // a lane that stops inside a chunk writes its state there
   static constexpr uint32_t D = 7654321u, M = 16777213u, MASK = 0xFFFFFFu;
   // the paper works on floats that are multiples of 2^-24: X * 2^-24, exact
   static __device__ float paper_f32(uint32_t u) { return (float)u * 0x1p-24f; }
@@ -587,13 +584,6 @@ struct Ranmar {
     si_ = si;
     stored_ = false;
     vbeg = 0;
-  }
-  // where a lane that stops mid-chunk writes its final state (nullptr: nowhere)
-  __device__ void retarget(uint32_t* st, uint64_t sn, uint64_t si) {
-    st_ = st;
-    sn_ = sn;
-    si_ = si;
-    stored_ = st == nullptr;
   }
   __device__ void store(uint32_t* st, uint64_t sn, uint64_t si, uint32_t, uint32_t) {
     if (stored_) return;
@@ -828,7 +818,7 @@ struct Ranlux {
   // (b^-(24-k) from aux), apply the segment's multiplier, convert back.  The
   // result sits at a block boundary: ring slot 0, borrow folded into S.
   __device__ uint32_t load_jumped(const uint32_t* st, uint64_t sn, uint64_t si, const uint32_t* jd,
-                                  const uint32_t* aux, uint32_t*) {
+                                  const uint32_t* aux) {
     uint32_t S[18], A[18];
     const uint32_t k0 = lcg_at_block_end(st, sn, si, aux, S);
 #pragma unroll
@@ -1426,7 +1416,7 @@ __device__ __forceinline__ void lane_loop(G& g, uint32_t* stage, int lane, uint3
         emit_general<G, DT, T>(st, lane, lo, q, ebeg, vend);
       }
     } else {
-      if constexpr (requires { g.retarget(nullptr, 0, 0); }) {
+      if constexpr (requires { G::kStoresInChunk; }) {
         g.template chunk<true>(lo, gbeg, vend, sink);
       } else {
         // lanes without a stream run along on their zero state
@@ -1500,7 +1490,7 @@ __device__ __forceinline__ void lane_task(uint32_t* stage, int lane, const Table
       g.load(rw.state, rw.sn, rw.si, k0);
       gbeg = k0;
     } else {
-      k0 = g.load_jumped(rw.state, rw.sn, rw.si, rw.jump + (j - 1u) * rw.jstride, aux, stage + lane);
+      k0 = g.load_jumped(rw.state, rw.sn, rw.si, rw.jump + (j - 1u) * rw.jstride, aux);
       gbeg = j * S;
     }
     constexpr bool f64 = DT == F64;
@@ -1532,7 +1522,6 @@ __device__ __forceinline__ void lane_task(uint32_t* stage, int lane, const Table
   } else {
     g.zero();
   }
-  if constexpr (requires { g.retarget(wst, wsn, wsi); }) g.retarget(last ? wst : nullptr, wsn, wsi);
   wave_sync();
   lane_loop<G, DT, false, SPLIT>(g, stage, lane, gbeg, ebeg, vend, q, false, 0);
   if (live && last) g.store(wst, wsn, wsi, gbeg, vend);

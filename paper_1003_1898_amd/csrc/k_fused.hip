@@ -255,7 +255,8 @@ hipError_t launch_fused(int kind, uint32_t p, uint32_t* st, uint64_t n, uint64_t
     case RANECU:
       return launch_split_fused<Ranecu<kSplitT>, Ranecu<>>(kRanecuDrawUs, st, n, draws, sum, hist, acc, s);
     case RANMAR:
-      if (n > kWaveStreams || ranmar_consumer_per_lane(n, draws)) return launch_lane_fused<Ranmar<>>(p, st, n, draws, sum, hist, acc, s);
+      if (n > kWaveStreams || ranmar_consumer_per_lane(n, draws))
+        return launch_lane_fused<Ranmar<>>(p, st, n, draws, sum, hist, acc, s);
       return launch_ranmar_fused(st, n, draws, sum, hist, acc, s);
     case RANLUX:
       return launch_lane_fused<Ranlux<>>(p, st, n, draws, sum, hist, acc, s);

@@ -199,6 +199,7 @@ struct LaneStart {
 
 // GGL: the output of position v is X_{v+1} = a^{v+1} X_0.
 struct LeapGgl {
+  using Steps = Ggl<>;  // the same recurrence, with the map of q steps
   static constexpr int BITS = 31;
   static constexpr bool kNtOut = false;
   static constexpr uint32_t A = 16807u, AL = (uint32_t)cpowmod(A, kLeapBlock - 3, 2147483647u);
@@ -223,11 +224,7 @@ struct LeapGgl {
     st[si] = y;
   }
   static __device__ float paper_f32(uint32_t u) { return Ggl<>::paper_f32(u); }
-  // the map of q steps, for the host (j0, j1), and its w-fold application
-  static void q_map(uint64_t q, uint64_t& j0, uint64_t& j1) {
-    j0 = cpowmod(A, q, 2147483647u);
-    j1 = 0;
-  }
+  // the map of q steps, w times over
   __device__ void advance_q(uint64_t j0, uint64_t, uint32_t w) {
     for (uint32_t i = 0; i < w; ++i) x = mulmod_2p31<1u>(x, (uint32_t)j0);
   }
@@ -235,6 +232,7 @@ struct LeapGgl {
 
 // RANECU: both MLCGs leap; the draw combines the two states.
 struct LeapRanecu {
+  using Steps = Ranecu<>;  // the same recurrence, with the map of q steps
   static constexpr int BITS = 31;
   static constexpr bool kNtOut = true;  // two MLCG steps per draw between the stores
   static constexpr uint32_t A1 = 40014u, A2 = 40692u;
@@ -277,10 +275,6 @@ struct LeapRanecu {
     st[sn + si] = b;
   }
   static __device__ float paper_f32(uint32_t u) { return Ranecu<>::paper_f32(u); }
-  static void q_map(uint64_t q, uint64_t& j0, uint64_t& j1) {
-    j0 = cpowmod(A1, q, 2147483563u);
-    j1 = cpowmod(A2, q, 2147483399u);
-  }
   __device__ void advance_q(uint64_t j0, uint64_t j1, uint32_t w) {
     for (uint32_t i = 0; i < w; ++i) {
       s1 = mulmod_2p31<85u>(s1, (uint32_t)j0);
@@ -292,6 +286,7 @@ struct LeapRanecu {
 // DRAND48 / RANNYU: the draw is X >> 16 of the 48-bit state.
 template <uint64_t A, uint64_t C>
 struct LeapLcg48 {
+  using Steps = Lcg48<128, A, C>;  // the same recurrence, with the map of q steps
   static constexpr int BITS = 32;
   static constexpr bool kNtOut = false;
   static constexpr uint64_t M = (1ull << 48) - 1;
@@ -325,11 +320,6 @@ struct LeapLcg48 {
     for (uint32_t i = 0; i < j; ++i) y = (A * y + C) & M;
     st[si] = (uint32_t)y;
     st[sn + si] = (uint32_t)(y >> 32);
-  }
-  static void q_map(uint64_t q, uint64_t& j0, uint64_t& j1) {
-    const Affine48 f = caffine_pow(A, C, q);
-    j0 = f.a;
-    j1 = f.c;
   }
   __device__ void advance_q(uint64_t j0, uint64_t j1, uint32_t w) {
     for (uint32_t i = 0; i < w; ++i) x = (j0 * x + j1) & M;
@@ -445,7 +435,7 @@ hipError_t launch_leap_rows(int dtype, uint32_t* st, uint64_t sn, uint64_t n, ui
     const uint64_t Q = ((draws + 3) / 4 + kLeapBlock - 1) / kLeapBlock * kLeapBlock;
     const uint32_t q = (uint32_t)Q;
     uint64_t j0 = 0, j1 = 0;
-    L::q_map(Q, j0, j1);
+    L::Steps::q_map(Q, j0, j1);
     switch (dtype) {
       case U32:
         hipLaunchKernelGGL((k_leap_quarters<L, U32, QUADS>), grid, block, 0, s, st, sn, n, d, q, j0, j1, out, row_elems,
@@ -697,7 +687,8 @@ hipError_t launch_generate(int kind, uint32_t p, uint32_t* st, uint64_t n, uint6
     case RANECU:
       return launch_leap<LeapRanecu>(dtype, st, n, draws, out, row_elems, off, s);
     case RANMAR:
-      if (ranmar_row_per_lane(n, draws)) return launch_lane_gen<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      if (ranmar_row_per_lane(n, draws))
+        return launch_lane_gen<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
       return launch_ranmar(dtype, st, n, draws, out, row_elems, off, s);
     case DRAND48:
       return launch_leap<LeapLcg48<25214903917ull, 11u>>(dtype, st, n, draws, out, row_elems, off, s);
@@ -765,7 +756,8 @@ hipError_t launch_generate_packed(int kind, uint32_t p, uint32_t* st, uint64_t n
     case RANECU:
       return launch_leap_pack<Ranecu<>>(dtype, st, n, draws, out, row_elems, off, s);
     case RANMAR:
-      if (ranmar_packed_per_lane(n, draws)) return launch_lane_pack<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
+      if (ranmar_packed_per_lane(n, draws))
+        return launch_lane_pack<Ranmar<>>(dtype, p, st, n, draws, out, row_elems, off, s);
       return launch_ranmar_packed(dtype, st, n, draws, out, row_elems, off, s);
     case RANLUX:
       return launch_lane_pack<Ranlux<96>>(dtype, p, st, n, draws, out, row_elems, off, s);

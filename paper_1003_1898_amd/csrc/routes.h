@@ -124,7 +124,9 @@ inline bool mt_row_per_wave(uint64_t n, uint64_t draws) {
   if (draws >= (even ? 8192u : 6500u)) return !even && n < 32768;
   if (n <= 18000) return true;
   const uint64_t bytes = n * (kMtStateBytes + 4 * draws);
-  return bytes <= (n <= 22528 ? 300'000'000u : n > 80000 ? 264'500'000u : even || n > 40000 ? 280'000'000u : 305'000'000u);
+  if (n <= 22528) return bytes <= 300'000'000u;
+  if (n > 80000) return bytes <= 264'500'000u;
+  return bytes <= (even || n > 40000 ? 280'000'000u : 305'000'000u);
 }
 
 // --------------------------------------------------------------------- RANMAR
