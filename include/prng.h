@@ -149,11 +149,11 @@ uint64_t prng_n_streams(const prng_gen *g);
  * calls continue the streams: generate(a) then generate(b) writes exactly the
  * elements generate(a + b) would.  dtype PRNG_U32, PRNG_F32, PRNG_F64 or
  * PRNG_F32_PAPER.
- * RANLUX and XOR128 objects cut long requests into segments started from
- * jumped-ahead states (same output), so that several wavefronts per SIMD
- * run: the call copies the state into the object's scratch area on `stream`
- * first and takes the jumps from tables written by prng_create, so it stays
- * asynchronous and can be captured into a graph. */
+ * RANLUX and XOR128 objects cut requests from some 200 draws on, where that is
+ * faster, into segments started from jumped-ahead states (same output), so
+ * that more wavefronts run: the call copies the state into the object's
+ * scratch area on `stream` first and takes the jumps from tables written by
+ * prng_create, so it stays asynchronous and can be captured into a graph. */
 int prng_generate(prng_gen *g, uint64_t count, int dtype, void *d_out, size_t out_bytes, void *stream);
 
 /* prng_generate for callers that cannot allocate device memory or take an
@@ -321,9 +321,10 @@ size_t prng_table_tune_work_bytes(prng_gen *const *gens, int n_gens, const prng_
 /* One run of the table on `stream`.  use_graph != 0: the first call captures
  * the run (one kernel clearing the counters and copying the cut streams'
  * starting states, the MT19937 jump kernel, then the persistent kernels of
- * the two lane-per-stream classes -- GGL, XOR128, RANECU, DRAND48, RANNYU
- * and RANLUX; RANMAR -- and of MT19937, placed on streams by the concurrency
- * setting) into a HIP graph and every call launches that graph;
+ * the two lane classes -- GGL, XOR128, RANECU, DRAND48, RANNYU and RANLUX, a
+ * lane per segment; RANMAR, a wavefront per segment -- and of MT19937, placed
+ * on streams by the concurrency setting) into a HIP graph and every call
+ * launches that graph;
  * use_graph == 0 enqueues the kernels directly. */
 int prng_table_run(prng_table *t, int use_graph, void *stream);
 
@@ -337,13 +338,13 @@ int prng_table_run(prng_table *t, int use_graph, void *stream);
 int prng_table_autotune(prng_table *t, int repeats, void *stream);
 
 /* Current setting (grids in 256-thread blocks of four wavefronts; lane_grid
- * counts blocks of RANMAR's class, one per CU, 256 filling the chip; the
- * other lane class runs twice as many; an MT19937 block works on one segment
- * at a time).  concurrent: 0 runs the kernels
- * one after the other; 1 runs MT19937's beside the lane classes, which follow
- * one another; 2 gives MT19937 and every lane class a stream of its own, the
- * classes sharing the chip; 3 is 2 with the lane classes started before the
- * MT19937 jump kernel, which then runs on MT19937's stream. */
+ * 256 runs two blocks of the first lane class and sixteen of RANMAR's class
+ * per CU, other values in proportion; an MT19937 block works on one segment
+ * at a time).  concurrent: 0 runs the kernels one after the other; 1 runs
+ * MT19937's beside the lane classes, which follow one another; 2 gives MT19937
+ * and every lane class a stream of its own, the classes sharing the chip; 3 is
+ * 2 with the lane classes started before the MT19937 jump kernel, which then
+ * runs on MT19937's stream. */
 int prng_table_get_config(const prng_table *t, int *lane_grid, int *mt_grid, int *concurrent);
 /* Override the setting (drops a captured graph); PRNG_EINVAL for grids
  * outside [1, 65536] or concurrent outside 0..3. */

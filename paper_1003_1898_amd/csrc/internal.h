@@ -200,10 +200,10 @@ hipError_t launch_ranmar_fused(uint32_t* state, uint64_t n, uint64_t draws, uint
 // snapshot rows, in one kernel.
 hipError_t launch_table_prepare(uint32_t* counters, int n_counters, const SnapRow* rows, uint32_t n,
                                 uint32_t max_words, hipStream_t s);
-// Lane-per-stream task classes of the stream table and the blocks (of four
-// wavefronts) that fill the chip for each: GGL/XOR128/RANECU/DRAND48/RANNYU
-// and RANLUX (its 96-draw chunks staged in three bytes), two per CU; RANMAR,
-// whose kernel takes a segment per wavefront and sixteen times these blocks.
+// Lane classes of the stream table and their full grids, in blocks of four
+// wavefronts: GGL/XOR128/RANECU/DRAND48/RANNYU and RANLUX (its 96-draw chunks
+// staged in three bytes), a lane per segment, two blocks per CU; RANMAR, whose
+// kernel takes a segment per wavefront and sixteen times these blocks.
 constexpr int kLaneClasses = 2;
 constexpr int kClassFullGrid[kLaneClasses] = {512, 256};
 inline int lane_class(int kind) { return kind == RANMAR ? 1 : 0; }

@@ -63,9 +63,11 @@ __global__ __launch_bounds__(256) void k_lane_fused(uint32_t* __restrict__ state
 //
 // One lane per stream (k_lane_fused) runs ceil(n / 64) wavefronts, 64 of them
 // at 4096 streams, one dependent step after the other; here every SIMD has
-// work from about 1024 / W streams on, and the bound is VALU issue (RANECU:
-// 20 instructions per draw).  4096 streams x 2^20 draws of RANECU: 46.0 ms
-// before, 2.06 ms now (2.1e12 draws/s); 2^30 draws of GGL 0.27 ms.
+// work from about 1024 / W streams on, and the bound is VALU issue.  RANECU takes
+// 20 instructions per draw, 72 cycles of a SIMD for a wavefront's (2.4 for an
+// addition or a mask, 4.2 for the others), which is 2.0 ms for 2^32 draws at 2.35
+// GHz.  4096 streams x 2^20 draws of RANECU: 46.0 ms with one lane per stream,
+// 2.0 ms so (2.1e12 draws/s); 2^30 draws of GGL 0.27 ms.
 //
 // The histogram has 32 columns of 64 bins: the LDS takes a wavefront in halves
 // of 32 lanes, so lanes l and l + 32 share a column without a bank conflict,

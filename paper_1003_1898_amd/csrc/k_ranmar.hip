@@ -33,7 +33,7 @@ struct StateTile {
 // R streams per wavefront, one after the other (R = 1: states read and written
 // directly).  Bound by LDS latency at few streams (four dependent steps per
 // 256 positions) and by the row stores at many.  f32, one lane per stream
-// before: 256 streams x 4096 151.9 -> 7.8 us, 4096 x 1000 54.9 -> 8.2 us,
+// before: 256 streams x 4096 151 -> 7.0 us, 4096 x 1000 54.9 -> 8.2 us,
 // 16384 x 4096 154.6 -> 48.4 us (5.8 TB/s).  R = 2 over R = 1 at 65536 x 300:
 // 28.3 and 61.6 us (R = 4: 28.7, but 11.6 instead of 8.2 us at 4096 x 1000).
 template <int DT, int R>

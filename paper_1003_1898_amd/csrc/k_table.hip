@@ -148,7 +148,8 @@ constexpr int kJumpThreads = 1024;  // four teams of 256 split each pattern's gr
 constexpr int kJumpQ = 6, kJumpPatterns = 1 << kJumpQ;
 constexpr int kJumpGroups = (19937 + kJumpQ - 1) / kJumpQ;
 constexpr int kJumpSpan = 624 + kJumpQ - 1;      // words a group is read for
-constexpr int kJumpZero = kMtSeqWords + 8;       // zeros, for the padding groups (a last group reads two words past the sequence)
+// zeros, for the padding groups (the last group reads a word past the sequence)
+constexpr int kJumpZero = kMtSeqWords + 8;
 constexpr int kJumpPitch = kJumpSpan + 3;
 constexpr int kJumpRound = 16;                   // groups per round: four of each team
 constexpr int kJumpList = (kJumpGroups + (kJumpPatterns - 1) * (kJumpRound - 1) + 7) / 8 * 8;
@@ -283,7 +284,7 @@ hipError_t launch_table_lane(int cls, const TableTask* tasks, uint32_t ntasks, c
                              const uint32_t* tails, uint32_t* counter, const uint32_t* aux, int grid, hipStream_t s) {
   if (cls == 0)
     hipLaunchKernelGGL(k_table_lane, dim3(grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter, aux);
-  else  // RANMAR: a wavefront per segment, up to sixteen blocks per CU
+  else  // RANMAR: a wavefront per segment; at most sixteen blocks per CU, of which eight are resident at a time
     hipLaunchKernelGGL(k_table_ranmar, dim3(16 * grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter);
   return hipGetLastError();
 }

@@ -88,9 +88,10 @@ inline bool xor128_long_segments(uint64_t n, uint64_t d) {
 // power of two leaves only those of the segment's number.  f64 4096 x 2000 127
 // us uncut, 34 us in 32 segments.  The copy of the states and a jump cost about
 // as much as 200 draws, less where the uncut call would end inside a 128-draw
-// chunk.  Uncut and in segments of 128, f32: 4096 x 256 10.1 and 13.0 us, x 300
-// 15.1 and 14.4, x 384 14.1 and 13.2, x 512 18.1 and 16.4; 20011 x 256 12.1 and
-// 15.0, x 320 17.1 and 15.2, x 512 19.8 and 20.6, x 640 23.4 and 21.2.
+// chunk.  Uncut and in segments of 128, f32: 4096 x 192 11.5 and 11.0 us, x 224
+// 12.0 and 16.1, x 256 10.1 and 13.0, x 300 15.1 and 14.4, x 384 14.1 and 13.2, x
+// 512 18.1 and 16.4; 20011 x 256 12.1 and 15.0, x 320 17.1 and 15.2, x 512 19.8 and
+// 20.6, x 640 23.4 and 21.2.
 // `shared`: the snapshot area is every call's of the GPU, and short calls leave it alone.
 inline Cut xor128_cut(uint64_t n, uint64_t d, bool shared) {
   const uint64_t waves = (n + 63) / 64;
@@ -98,7 +99,7 @@ inline Cut xor128_cut(uint64_t n, uint64_t d, bool shared) {
   if (xor128_long_segments(n, d)) {
     const uint64_t K = std::min<uint64_t>({8, (4096 + waves - 1) / waves, std::max<uint64_t>(1, d / 2048)});
     S = ((d + K - 1) / K + 127) / 128 * 128;
-  } else if (shared ? d >= 4096 : d > (n < 16384 ? 256u : 512u) || (d > 300 && d % 128 != 0)) {
+  } else if (shared ? d >= 4096 : d > (n < 16384 ? 256u : 512u) || (d > 300 && d % 128 != 0) || d == 192) {
     const uint64_t want = 2048 / waves;
     S = std::max<uint64_t>(128, std::bit_ceil((d + want - 1) / want));
   }

@@ -343,7 +343,7 @@ void drop_graph(prng_table* t) {
 // class on a stream of its own, so that a class whose tasks run out leaves its
 // part of the chip to the others; 3: as 2, but
 // the lane classes start before the MT19937 jumps, which run on MT19937's
-// stream (a few 1024-thread blocks with 88 KB of LDS each that otherwise hold
+// stream (a few 1024-thread blocks with 95 KB of LDS each that otherwise hold
 // the chip alone).  Forked streams join `s` at the end.
 hipError_t prng::enqueue_run(prng_table* t, hipStream_t s) {
   hipError_t e = launch_table_prepare(t->d_counters, kLaneClasses + 1, t->d_snaps, t->n_snaps, t->snap_words, s);
@@ -387,7 +387,7 @@ hipError_t prng::enqueue_run(prng_table* t, hipStream_t s) {
     }
     return hipSuccess;
   };
-  // cfg.lane_grid: blocks of the one-per-CU class; 256 fill the chip
+  // cfg.lane_grid: 256 for the class's full grid
   auto lane_grid_of = [&](int c) {
     const int full = kClassFullGrid[c] * t->cfg.lane_grid / 256;
     return std::max(1, std::min<int>(full, (int)((t->n_class_tasks[c] + 3) / 4)));

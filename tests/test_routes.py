@@ -38,7 +38,7 @@ def test_xor128_short_calls_stay_uncut(routes, n, d):
     assert routes("xor128", [(n, d, 0)])[0][1] == 1
 
 
-@pytest.mark.parametrize("n,d,K", [(256, 384, 3), (4096, 512, 4), (4096, 4000, 32), (20011, 448, 4), (20011, 2048, 4),
+@pytest.mark.parametrize("n,d,K", [(256, 192, 2), (256, 384, 3), (4096, 512, 4), (4096, 4000, 32), (20011, 448, 4), (20011, 2048, 4),
                                    (1024, 32768, 128)])
 def test_xor128_short_segments(routes, n, d, K):
     S, got = routes("xor128", [(n, d, 0)])[0]
