@@ -2,9 +2,9 @@
 // Device code shared by the HIP translation units of libprng (gfx950,
 // MI355X): generators, output staging and emission, the lane loop, the
 // stream-table task decoder and the MT19937 block machinery.  The kernels
-// and their launchers live in k_plain.hip, k_lux.hip, k_fused.hip,
+// and their launchers live in k_plain.hip, k_ranmar.hip, k_lux.hip, k_fused.hip,
 // k_table.hip and k_init.hip; each includes this header (everything here is
-// internal to its translation unit).
+// internal to its translation unit).  routes.h says which kernel a call takes.
 //
 // Bulk uniform generation for the six
 // generators of arXiv:1003.1898 (GGL, XOR128, RANECU, RANMAR, RANLUX, MT19937)
@@ -14,8 +14,8 @@
 // ------------------
 // * GGL, RANECU, DRAND48, RANNYU: plain rows leap, a wavefront per stream
 //   (k_plain.hip); RANMAR and MT19937 keep a stream's window in LDS and step it
-//   with a wavefront (RanmarWave, mt_twist_emit) or, for long MT19937 launches,
-//   a workgroup.
+//   with a wavefront (RanmarWave, mt_twist_emit) or, for MT19937 launches past
+//   the last-level cache, a workgroup.
 // * XOR128 and RANLUX, and the other lane kinds in the stream table and where
 //   their streams fill the chip: one lane per stream
 //   (Section 3.1: independent sequences, one lag table per instance).  The
