@@ -389,14 +389,13 @@ typedef struct prng_server prng_server;
  * max_inflight in [1, 16] batches; max_batch >= 1 requests per batch.
  * seg_len: a base length L, PRNG_SEG_AUTO (L = 384) or a length rounded up
  * to a multiple of 384; segments are 2 L positions for GGL, RANECU, DRAND48
- * and RANNYU, 4 L for XOR128, L / 2 for RANLUX (at least 384, a multiple of
- * 384: its draws cost about four of the others', and a batch lasts as long as
- * its longest task), 32 L for RANMAR, whose segments are a wavefront's, and
- * 512 L for MT19937 (a multiple of 624); PRNG_SEG_NEVER: one lane, wavefront
- * (RANMAR) or workgroup (MT19937) per request, as a plain per-stream kernel.
- * max_request_draws: the largest request in draws (two per fp64 element), at
- * most 2^30 and at most 32768 segments (for RANMAR 32768 times 4 L draws).
- * Synchronous; starts the worker thread. */
+ * and RANNYU, 4 L for XOR128, L / 2 for RANLUX (at least 384, a multiple of 384: its
+ * draws cost about four of the others', and a batch lasts as long as its
+ * longest task), 4 L for RANMAR and 512 L for MT19937 (a multiple of 624);
+ * PRNG_SEG_NEVER: one lane or workgroup per request, as a plain per-stream
+ * kernel.  max_request_draws: the largest request in draws (two per fp64
+ * element), at most 2^30 and at most 32768 segments.  Synchronous; starts the
+ * worker thread. */
 int prng_server_create(prng_server **s, prng_gen *const *gens, int n_gens, void *d_pool, size_t pool_bytes,
                        int max_inflight, int max_batch, uint32_t seg_len, uint64_t max_request_draws);
 /* Queue n requests (host arrays).  arrive_ns: scheduled arrival of each (an

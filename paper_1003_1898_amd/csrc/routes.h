@@ -172,13 +172,6 @@ inline bool ranmar_consumer_per_lane(uint64_t n, uint64_t draws) {
   return n >= 17000 && n <= 36000 && draws <= (n >= 24000 ? 512u : 256u);
 }
 
-// Server: draws of a request's segment for a base length L.  A segment is a
-// wavefront's and starts with a jump that takes as long as about 500 draws and
-// reads the stream's 98 state words, a line each.  Closed batches of 21000
-// requests at 4, 8, 16, 32, 64 and 128 L (L = 384): 1.15, 1.48, 1.67, 1.72, 1.73
-// and 1.73 TB/s.
-inline uint64_t server_ranmar_segment(uint64_t L) { return 32 * L; }
-
 // ------------------------------------------ interleaved rows of the leap kinds
 // GGL, RANECU, DRAND48 and RANNYU leap along a row of four streams, after up to
 // ten products per stream that bring a lane to its place: RANECU, whose states

@@ -66,8 +66,9 @@ class ServerJumps : public JumpSource {
   // small next to the draws it saves.  GGL, RANECU, DRAND48 and RANNYU 2 L;
   // XOR128 4 L (its resident jump data is a 128 x 128 GF(2) matrix, 2 KB, per
   // segment of the longest request); RANLUX (576-bit products) L / 2, at
-  // least 384 and a multiple of 384; RANMAR server_ranmar_segment(L); MT19937 (a
-  // window built from ~10^4 others over a whole CU) 512 L, a multiple of 624.
+  // least 384 and a multiple of 384; RANMAR (97^2 multiply-adds, a class of
+  // its own) 4 L; MT19937 (a window built from ~10^4 others over a whole CU)
+  // 512 L, a multiple of 624.
   uint64_t seg_len(int kind) const override {
     if (!L) return 0;
     switch (kind) {
@@ -76,7 +77,7 @@ class ServerJumps : public JumpSource {
       case XOR128:
         return 4 * L;
       case RANMAR:
-        return server_ranmar_segment(L);
+        return 4 * L;
       case MT19937:
         return (std::max<uint64_t>(512 * L, 1248) + 623) / 624 * 624;
       default:
@@ -365,9 +366,9 @@ PRNG_API int prng_server_create(prng_server** out, prng_gen* const* gens, int n_
       if (offs.count(key)) continue;
       const uint64_t Lk = S->jumps.seg_len(g->kind);
       const uint64_t K = (max_request_draws + Lk - 1) / Lk;  // segments of the longest request
-      const uint64_t most = kServerMaxSegments * (g->kind == RANMAR ? 4 * L : Lk);  // longest request
-      if (max_request_draws > most)
-        return fail(PRNG_EINVAL, "max_request_draws above %llu for this segment length", (unsigned long long)most);
+      if (K > kServerMaxSegments)
+        return fail(PRNG_EINVAL, "max_request_draws above %llu for this segment length",
+                    (unsigned long long)(kServerMaxSegments * Lk));
       const uint32_t nj = (uint32_t)(K - 1);  // segments j = 1..K-1 start from jumped states
       const uint32_t stride = jump_slot_words(g->kind);
       offs[key] = host.size();

@@ -29,8 +29,6 @@ int main() {
       const double us[] = {0, prng::kGglDrawUs, prng::kXor128DrawUs, prng::kRanecuDrawUs, 0, 0, 0, prng::kDrand48DrawUs,
                            prng::kRannyuDrawUs};
       printf("%d\n", prng::consumer_width(us[x], x == 2, n, d));
-    } else if (rule == "server_ranmar") {
-      printf("%llu\n", (unsigned long long)prng::server_ranmar_segment(n));
     } else if (rule == "ranges") {
       prng::for_stream_ranges(n, d, [](uint64_t s0, uint64_t m) {
         printf("%llu %llu ", (unsigned long long)s0, (unsigned long long)m);

@@ -113,12 +113,6 @@ def test_ranmar_consumer(routes, n, d, lane):
     assert routes("ranmar_consumer", [(n, d, 0)]) == [[lane]]
 
 
-@pytest.mark.parametrize("L", [384, 768, 6144])
-def test_server_ranmar_segments_outweigh_their_jumps(routes, L):
-    ((length,),) = routes("server_ranmar", [(L, 0, 0)])
-    assert length % L == 0 and length >= 20 * 500  # a jump takes as long as about 500 draws
-
-
 # ------------------------------------------ interleaved rows of the leap kinds
 @pytest.mark.parametrize("n,d,ranecu,lane", [(65536, 128, 1, 1), (65536, 256, 1, 1), (65536, 512, 1, 1),
                                              (65536, 1024, 1, 0), (40000, 384, 1, 0), (16384, 256, 1, 0),
