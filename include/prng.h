@@ -338,13 +338,13 @@ int prng_table_run(prng_table *t, int use_graph, void *stream);
 int prng_table_autotune(prng_table *t, int repeats, void *stream);
 
 /* Current setting (grids in 256-thread blocks of four wavefronts; lane_grid
- * 256 runs two blocks of the first lane class and sixteen of RANMAR's class
- * per CU, other values in proportion; an MT19937 block works on one segment
- * at a time).  concurrent: 0 runs the kernels one after the other; 1 runs
- * MT19937's beside the lane classes, which follow one another; 2 gives MT19937
- * and every lane class a stream of its own, the classes sharing the chip; 3 is
- * 2 with the lane classes started before the MT19937 jump kernel, which then
- * runs on MT19937's stream. */
+ * 256 runs two blocks of the first lane class per CU, other values in
+ * proportion; RANMAR's class has a wavefront per segment whatever it is; an
+ * MT19937 block works on one segment at a time).  concurrent: 0 runs the
+ * kernels one after the other; 1 runs MT19937's beside the lane classes, which
+ * follow one another; 2 gives MT19937 and every lane class a stream of its own,
+ * the classes sharing the chip; 3 is 2 with the lane classes started before the
+ * MT19937 jump kernel, which then runs on MT19937's stream. */
 int prng_table_get_config(const prng_table *t, int *lane_grid, int *mt_grid, int *concurrent);
 /* Override the setting (drops a captured graph); PRNG_EINVAL for grids
  * outside [1, 65536] or concurrent outside 0..3. */

@@ -1093,6 +1093,15 @@ __device__ __forceinline__ void quad_emit(uint64_t row, uint32_t v, const uint32
   }
 }
 
+// Workgroup index under which each run of Q consecutive ones is on one XCD
+// (workgroups go to the eight XCDs in turn), so that the 128-byte lines of the
+// state rows, 32 streams each, are not fetched by all eight of them.
+template <uint32_t Q>
+__device__ __forceinline__ uint32_t xcd_block() {
+  const uint32_t b = blockIdx.x, i = b % (8u * Q);
+  return b - i + 8u * Q > gridDim.x ? b : b - i + (i % 8u) * Q + i / 8u;
+}
+
 // `draws` positions of a RANMAR stream by one wavefront, whose ring holds the
 // window of a state with C = c0, to the row at byte address `row`.
 struct RanmarOut {  // quad_emit's generator traits

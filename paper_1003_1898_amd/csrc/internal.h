@@ -200,12 +200,12 @@ hipError_t launch_ranmar_fused(uint32_t* state, uint64_t n, uint64_t draws, uint
 // snapshot rows, in one kernel.
 hipError_t launch_table_prepare(uint32_t* counters, int n_counters, const SnapRow* rows, uint32_t n,
                                 uint32_t max_words, hipStream_t s);
-// Lane classes of the stream table and their full grids, in blocks of four
-// wavefronts: GGL/XOR128/RANECU/DRAND48/RANNYU and RANLUX (its 96-draw chunks
-// staged in three bytes), a lane per segment, two blocks per CU; RANMAR, whose
-// kernel takes a segment per wavefront and sixteen times these blocks.
+// Lane classes of the stream table: GGL/XOR128/RANECU/DRAND48/RANNYU and RANLUX
+// (its 96-draw chunks staged in three bytes), a lane per segment, in persistent
+// blocks of four wavefronts, two per CU at the full grid; RANMAR, a wavefront
+// per segment (`grid` and `counter` of launch_table_lane are the first's).
 constexpr int kLaneClasses = 2;
-constexpr int kClassFullGrid[kLaneClasses] = {512, 256};
+constexpr int kLaneFullGrid = 512;
 inline int lane_class(int kind) { return kind == RANMAR ? 1 : 0; }
 hipError_t launch_table_lane(int cls, const TableTask* tasks, uint32_t ntasks, const TableRow* rows,
                              const uint32_t* tails, uint32_t* counter, const uint32_t* aux, int grid, hipStream_t s);

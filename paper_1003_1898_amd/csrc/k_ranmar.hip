@@ -5,15 +5,6 @@
 namespace prng {
 namespace {
 
-// Workgroup index under which each run of Q consecutive ones is on one XCD
-// (workgroups go to the eight XCDs in turn), so that the 128-byte lines of the
-// state rows, 32 streams each, are not fetched by all eight of them.
-template <uint32_t Q>
-__device__ __forceinline__ uint32_t xcd_block() {
-  const uint32_t b = blockIdx.x, i = b % (8u * Q);
-  return b - i + 8u * Q > gridDim.x ? b : b - i + (i % 8u) * Q + i / 8u;
-}
-
 // States of a workgroup's 4 R consecutive streams, moved through LDS as 4 R
 // adjacent words of each of the 98 state rows.
 template <int R>

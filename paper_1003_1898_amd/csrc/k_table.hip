@@ -36,22 +36,26 @@ __global__ __launch_bounds__(256) void k_table_lane(const TableTask* __restrict_
   }
 }
 
-// RANMAR tasks, segment by segment: a wavefront pulls one segment of a task's
-// (up to 64) at a time, so that a task's segments spread over the chip, and
-// generates it as the plain kernel does.  The jump costs about as much as 500
-// draws (97 reads and products for 97 window values); one lane per segment,
-// as the other kinds run, it costs 20k operations per lane and the window and
-// its chunk take a SIMD's registers for a single wavefront.
+// RANMAR tasks, a segment per wavefront: wavefront v takes segment v mod 64 of
+// task v / 64 and generates it as the plain kernel does.  The jump costs about as
+// much as 500 draws (97 reads and products for 97 window values); one lane per
+// segment, as the other kinds run, it costs 20k operations per lane and the window
+// and its chunk take a SIMD's registers for a single wavefront.  The grid holds a
+// wavefront per segment (up to 2^25 of them), which the dispatcher spreads: a task
+// counter on which every wavefront drew its next segment took 15 ns a segment on
+// the whole chip (40000 rows of 64 draws 587 us).
 __global__ __launch_bounds__(256) void k_table_ranmar(const TableTask* __restrict__ tasks, uint32_t ntasks,
                                                       const TableRow* __restrict__ rows,
-                                                      const uint32_t* __restrict__ tails, uint32_t* counter) {
+                                                      const uint32_t* __restrict__ tails) {
   __shared__ __attribute__((aligned(16))) uint32_t ring_all[4][RanmarWave::kRing];
   const int lane = threadIdx.x & 63;
   RanmarWave w(ring_all[threadIdx.x >> 6], lane);
-  for (uint32_t u = next_task(counter, lane); u / 64u < ntasks; u = next_task(counter, lane)) {
-    const TableTask& task = tasks[u / 64u];
-    if (u % 64u >= uni(task.nseg)) continue;
-    const uint64_t g = task.g0 + u % 64u;
+  // a task's sixteen workgroups, whose streams share the state's lines, on one XCD
+  for (uint64_t v = (uint64_t)xcd_block<16>() * 4u + uni(threadIdx.x >> 6); v < 64ull * ntasks; v += 4ull * gridDim.x) {
+    const TableTask& task = tasks[v / 64u];
+    const uint32_t i = (uint32_t)(v % 64u);
+    if (i >= uni(task.nseg)) continue;
+    const uint64_t g = task.g0 + i;
     uint32_t r, j;
     if (task.tail) {
       r = uni(tails[g]);
@@ -284,8 +288,9 @@ hipError_t launch_table_lane(int cls, const TableTask* tasks, uint32_t ntasks, c
                              const uint32_t* tails, uint32_t* counter, const uint32_t* aux, int grid, hipStream_t s) {
   if (cls == 0)
     hipLaunchKernelGGL(k_table_lane, dim3(grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter, aux);
-  else  // RANMAR: a wavefront per segment; at most sixteen blocks per CU, of which eight are resident at a time
-    hipLaunchKernelGGL(k_table_ranmar, dim3(16 * grid), dim3(256), 0, s, tasks, ntasks, rows, tails, counter);
+  else  // sixteen workgroups per task of 64 segments
+    hipLaunchKernelGGL(k_table_ranmar, dim3(std::min<uint32_t>(ntasks, 1u << 19) * 16u), dim3(256), 0, s, tasks, ntasks,
+                       rows, tails);
   return hipGetLastError();
 }
 

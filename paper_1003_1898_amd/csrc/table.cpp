@@ -337,14 +337,14 @@ void drop_graph(prng_table* t) {
 }  // namespace
 
 // Enqueue one run: reset counters, copy the starting states of split streams,
-// build the jumped MT19937 windows, then the persistent kernels.  cfg.concurrent
-// 0: all of them one after the other; 1: the lane classes one after the
-// other, MT19937 beside them on a forked stream; 2: MT19937 and every lane
-// class on a stream of its own, so that a class whose tasks run out leaves its
-// part of the chip to the others; 3: as 2, but
-// the lane classes start before the MT19937 jumps, which run on MT19937's
-// stream (a few 1024-thread blocks with 95 KB of LDS each that otherwise hold
-// the chip alone).  Forked streams join `s` at the end.
+// build the jumped MT19937 windows, then the kernels of the classes.
+// cfg.concurrent 0: all of them one after the other; 1: the lane classes one
+// after the other, MT19937 beside them on a forked stream; 2: MT19937 and every
+// lane class on a stream of its own, so that a class whose tasks run out leaves
+// its part of the chip to the others; 3: as 2, but the lane classes start before
+// the MT19937 jumps, which run on MT19937's stream (a few 1024-thread blocks
+// with 95 KB of LDS each that otherwise hold the chip alone).  Forked streams
+// join `s` at the end.
 hipError_t prng::enqueue_run(prng_table* t, hipStream_t s) {
   hipError_t e = launch_table_prepare(t->d_counters, kLaneClasses + 1, t->d_snaps, t->n_snaps, t->snap_words, s);
   if (e != hipSuccess) return e;
@@ -387,16 +387,12 @@ hipError_t prng::enqueue_run(prng_table* t, hipStream_t s) {
     }
     return hipSuccess;
   };
-  // cfg.lane_grid: 256 for the class's full grid
-  auto lane_grid_of = [&](int c) {
-    const int full = kClassFullGrid[c] * t->cfg.lane_grid / 256;
-    return std::max(1, std::min<int>(full, (int)((t->n_class_tasks[c] + 3) / 4)));
-  };
   auto launch_lane = [&](int c) -> hipError_t {
     const uint32_t n = t->n_class_tasks[c];
     if (!n) return hipSuccess;
+    const int full = kLaneFullGrid * t->cfg.lane_grid / 256;  // cfg.lane_grid: 256 for the full grid
     return launch_table_lane(c, t->d_class_tasks[c], n, t->d_rows, t->d_tails, t->d_counters + c, t->d_aux,
-                             lane_grid_of(c), stream_of(c));
+                             std::max(1, std::min<int>(full, (int)((n + 3) / 4))), stream_of(c));
   };
   // mode 3: the lane classes do not wait for the MT19937 jumps, which run on
   // MT19937's stream; otherwise the jumps come first, over the whole chip
