@@ -35,31 +35,34 @@ constexpr uint32_t kLuxSplitMax = 64;  // segments of a stream at most
 
 // Whether segments from 96 draws on, about one wavefront per SIMD, beat the
 // fewest that lux_cut takes anyway.  The copy of the states and a jump take
-// about as long as 250 draws of p = 24, 150 of p = 97 and 100 of p = 389 (a
+// about as long as 200 draws of p = 24, 130 of p = 97 and 100 of p = 389 (a
 // draw's time is near p + 114 in some unit); against that stand the draws past
 // the first 96, and a second segment below 48 draws hides its jump behind the
 // first.  Few and many segments, f32, at 4096 streams: p = 24 x 256 19 and 24
-// us, x 384 19 and 22, x 576 26 and 22; p = 97 x 224 23 and 21, x 256 23 and 26,
-// x 384 33 and 28; p = 389 x 192 21 and 28, x 224 38 and 29.  More streams leave
-// less to gain: p = 24 20011 x 512 31 and 32 us, x 768 41 and 37; p = 97 20011 x
-// 384 34 and 33, 40000 x 512 43 and 46, x 3000 189 and 214; p = 24 40000 x 2048
-// 95 and 112; p = 389 40000 x 300 51 and 48.
-inline bool lux_short_segments(uint64_t waves, uint64_t d, uint32_t p) {
+// us, x 384 27 and 25 (from a block's start 19 and 22), x 576 26 and 22; p = 97 x
+// 224 23 and 21, x 256 23 and 26, x 384 33 and 28; p = 389 x 192 36 and 36, x 224
+// 38 and 29.  More streams leave less to gain: p = 24 20011 x 384 28 and 31 us, x
+// 768 41 and 37; p = 97 20011 x 256 25 and 29, x 384 34 and 33, 40000 x 512 43 and
+// 46, x 3000 189 and 214; p = 24 40000 x 2048 95 and 112; p = 389 40000 x 300 51
+// and 48.  f64 calls gain more: where an odd count has left the streams at odd
+// positions, a draw takes up to four times as long (p = 24 20011 x 4000 389 and
+// 227 us, p = 97 40000 x 3000 592 and 345).
+inline bool lux_short_segments(uint64_t waves, uint64_t d, uint32_t p, bool f64) {
   if (d <= 192) return false;
-  if (waves > 256 && p < 60 && d >= 3072) return false;  // cut already: 24000 x 3072 92 and 108 us
-  if (waves > 512 && p < 150) return false;
+  if (waves > 256 && p < 60 && d >= 3072 && !f64) return false;  // cut already: 24000 x 3072 92 and 108 us
+  if (waves > 512 && p < (f64 ? 60u : 150u)) return false;
   const uint64_t gain = (d - 96) * (p + 114ull) * (d <= 240 ? 2 : 1);
-  return gain >= (waves <= 256 ? 53500u : waves <= 512 ? 80000u : 100000u);
+  return gain >= (waves <= 256 ? 39000u : waves <= 512 ? 57000u : 100000u);
 }
 
 // The borrow chain runs one step at a time per lane, and the kernel needs two
 // wavefronts per SIMD to overlap it with the stores: about 2048 wavefronts where
 // a segment keeps 1536 draws.  Shorter segments, where they pay, are for calls
 // that own their snapshot area (not `shared`).  S is a multiple of 96.
-inline Cut lux_cut(uint64_t n, uint64_t d, uint32_t p, bool shared) {
+inline Cut lux_cut(uint64_t n, uint64_t d, uint32_t p, bool f64, bool shared) {
   const uint64_t waves = (n + 63) / 64;
   uint64_t K = std::min<uint64_t>({kLuxSplitMax, (2048 + waves - 1) / waves, std::max<uint64_t>(1, d / 1536)});
-  if (!shared && lux_short_segments(waves, d, p))
+  if (!shared && lux_short_segments(waves, d, p, f64))
     K = std::max(K, std::min<uint64_t>({kLuxSplitMax, (1024 + waves - 1) / waves, std::max<uint64_t>(1, d / 96)}));
   if (K == 1) return {d, 1};
   const uint64_t S = ((d + K - 1) / K + 95) / 96 * 96;
@@ -82,7 +85,9 @@ inline bool xor128_long_segments(uint64_t n, uint64_t d) {
 }
 
 // d draws of n streams.  Segments start from jumped states.
-// Long segments: at least 2048 draws, about 4096 wavefronts in all.
+// Long segments: at least 2048 draws, or two where fewer streams leave SIMDs idle
+// (20032 x 3072 68 us in two, 92 uncut; 28000 x 3072 100 and 94), about 4096
+// wavefronts in all.
 // Short ones: about 2048 wavefronts in segments of a power of two from 128 draws
 // on: a jump costs a matrix product (2 us) per set bit of its distance, and the
 // power of two leaves only those of the segment's number.  f64 4096 x 2000 127
@@ -97,7 +102,8 @@ inline Cut xor128_cut(uint64_t n, uint64_t d, bool shared) {
   const uint64_t waves = (n + 63) / 64;
   uint64_t S = d;
   if (xor128_long_segments(n, d)) {
-    const uint64_t K = std::min<uint64_t>({8, (4096 + waves - 1) / waves, std::max<uint64_t>(1, d / 2048)});
+    const uint64_t least = n < 26000 && d >= 3072 && !shared ? 2 : 1;
+    const uint64_t K = std::min<uint64_t>({8, (4096 + waves - 1) / waves, std::max<uint64_t>(least, d / 2048)});
     S = ((d + K - 1) / K + 127) / 128 * 128;
   } else if (shared ? d >= 4096 : d > (n < 16384 ? 256u : 512u) || (d > 300 && d % 128 != 0) || d == 192) {
     const uint64_t want = 2048 / waves;

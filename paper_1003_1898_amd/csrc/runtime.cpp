@@ -327,7 +327,7 @@ int generate_with(prng_gen* g, uint64_t count, int dtype, void* d_out, size_t ou
     const uint64_t c = count - off < max_elems ? count - off : max_elems;
     if (g->kind == RANLUX) {
       const uint64_t d = c * per;
-      const auto [S, K] = lux_cut(g->n, d, g->p, shared);
+      const auto [S, K] = lux_cut(g->n, d, g->p, dtype == F64, shared);
       uint32_t* snap = g->d_state;
       if (K > 1) {
         snap = snap_area;

@@ -12,8 +12,8 @@ int main() {
     if (rule == "xor128") {
       const prng::Cut c = prng::xor128_cut(n, d, x != 0);
       printf("%llu %llu\n", (unsigned long long)c.S, (unsigned long long)c.K);
-    } else if (rule == "lux" || rule == "lux_shared") {
-      const prng::Cut c = prng::lux_cut(n, d, (uint32_t)x, rule == "lux_shared");
+    } else if (rule == "lux" || rule == "lux_f64" || rule == "lux_shared") {
+      const prng::Cut c = prng::lux_cut(n, d, (uint32_t)x, rule == "lux_f64", rule == "lux_shared");
       printf("%llu %llu\n", (unsigned long long)c.S, (unsigned long long)c.K);
     } else if (rule == "mt19937") {
       printf("%d\n", (int)prng::mt_row_per_wave(n, d));

@@ -45,7 +45,7 @@ def test_xor128_short_segments(routes, n, d, K):
     assert got == K and S & (S - 1) == 0
 
 
-@pytest.mark.parametrize("n,d,K", [(12032, 8192, 4), (20032, 4096, 2), (24000, 16384, 8), (28000, 4096, 2),
+@pytest.mark.parametrize("n,d,K", [(12032, 8192, 4), (20011, 4000, 2), (28000, 3072, 1), (20032, 4096, 2), (24000, 16384, 8), (28000, 4096, 2),
                                    (32768, 1500, 1), (65536, 16384, 4)])
 def test_xor128_output_beyond_the_cache_takes_long_segments(routes, n, d, K):
     assert routes("xor128", [(n, d, 0)])[0][1] == K
@@ -60,7 +60,7 @@ def test_xor128_cuts_are_whole(routes):
 
 
 # ------------------------------------------------------------------ RANLUX rows
-@pytest.mark.parametrize("n,d,p", [(64, 192, 24), (4096, 256, 24), (256, 448, 24), (4096, 256, 97), (20011, 256, 97),
+@pytest.mark.parametrize("n,d,p", [(64, 192, 24), (4096, 256, 24), (256, 360, 24), (4096, 256, 97), (20011, 256, 97),
                                    (40000, 192, 223), (40000, 512, 97), (48000, 2304, 24), (40000, 3000, 97)])
 def test_ranlux_short_calls_stay_uncut(routes, n, d, p):
     assert routes("lux", [(n, d, p)])[0][1] == 1
@@ -73,13 +73,19 @@ def test_ranlux_segments(routes, n, d, p, K):
     assert routes("lux", [(n, d, p)])[0][1] == K
 
 
-@pytest.mark.parametrize("rule", ["lux", "lux_shared"])
+@pytest.mark.parametrize("n,d,p,K", [(4096, 192, 24, 1), (4096, 384, 24, 4), (40000, 3000, 97, 2),
+                                     (40000, 3000, 24, 1), (20011, 4000, 24, 4)])
+def test_ranlux_f64_segments(routes, n, d, p, K):
+    assert routes("lux_f64", [(n, d, p)])[0][1] == K
+
+
+@pytest.mark.parametrize("rule", ["lux", "lux_f64", "lux_shared"])
 def test_ranlux_cuts_are_whole(routes, rule):
     calls = _calls(2, 4000, 20, 30, (24, 48, 97, 223, 389, 800))
     for (n, d, p), (S, K) in zip(calls, routes(rule, calls)):
         assert (K - 1) * S < d <= K * S and 1 <= K <= 64, (n, d, p)
         assert K == 1 or (S % 96 == 0 and K * ((n + 255) // 256) < 1 << 24), (n, d, p)
-        assert rule == "lux" or K == 1 or d >= 3072, (n, d)
+        assert rule != "lux_shared" or K == 1 or d >= 3072, (n, d)
 
 
 # --------------------------------------------------------------- MT19937 rows
