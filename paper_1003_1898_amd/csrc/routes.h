@@ -186,7 +186,15 @@ inline bool ranmar_consumer_per_lane(uint64_t n, uint64_t draws) {
 // RANECU 65536 x 128 12 and 22, x 256 20 and 27, x 512 33 and 38, x 1024 70 and 60,
 // 40000 x 256 18 and 19, x 384 24 and 23; GGL 65536 x 128 10 and 12, x 256 15 and
 // 14, 32768 x 128 8 and 8, 44000 x 128 (a wavefront not full) 10 and 9.
+// A few draws pay for those products as much: RANECU 65536 x 24 14 and 16, x 48 17
+// and 19, 131072 x 24 26 and 29, 54848 x 35 14 and 16; 65536 x 8 12 and 13, x 64 21
+// and 20, 44032 x 32 14 and 12, 98304 x 32 26 and 23.
 inline bool leap_packed_per_lane(bool ranecu, uint64_t n, uint64_t draws) {
+  if (ranecu && draws >= 12 && draws <= 60) {
+    const uint64_t r = (n + 65535) / 65536;
+    return r * 65536 - n <= 16384 &&
+           (double)r * (10.1 + 0.075 * (double)draws) < 3.9 + (double)n * (11.2e-5 + 2.66e-6 * (double)draws);
+  }
   if (draws % 128) return false;
   if (!ranecu) return draws == 128 && (n % 64 ? n >= 56000 && n <= 65536 : n >= 38000);
   if (n % 64) return false;

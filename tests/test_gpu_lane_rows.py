@@ -1,7 +1,7 @@
 """Kernels that only many streams reach, at stream and draw counts that leave
 wavefronts, chunks of 128 draws and blocks ragged, several calls in a row: RANMAR
 by one lane per stream (plain and interleaved) and MT19937 rows of one workgroup
-per stream, every dtype; bit-exact with the oracle."""
+per stream, every dtype, and interleaved RANECU of a few draws; bit-exact with the oracle."""
 import numpy as np
 import pytest
 
@@ -34,6 +34,15 @@ def test_ranmar_interleaved_rows_of_lanes(oracle):
     for count, dt in ((127, "u32"), (129, "f32"), (128, "f32_paper"), (255, "f32_paper"), (1, "u32"), (256, "f32")):
         got = g.generate_packed4(count, dt).cpu().numpy().transpose(0, 2, 1).reshape(N, count)
         assert np.array_equal(bits(got), bits(oracle.generate("ranmar", st, count, dt, threads=8))), f"{count} {dt}"
+        assert np.array_equal(g.state_words(), st), f"state after {count} {dt}"
+
+
+@pytest.mark.parametrize("n", [57348, 65536])
+def test_ranecu_interleaved_rows_of_few_draws(oracle, n):
+    g, st = _new(oracle, "ranecu", n)
+    for count, dt in ((16, "u32"), (55, "f32"), (24, "f32_paper"), (33, "f32"), (56, "u32")):
+        got = g.generate_packed4(count, dt).cpu().numpy().transpose(0, 2, 1).reshape(n, count)
+        assert np.array_equal(bits(got), bits(oracle.generate("ranecu", st, count, dt, threads=8))), f"{count} {dt}"
         assert np.array_equal(g.state_words(), st), f"state after {count} {dt}"
 
 

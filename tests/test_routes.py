@@ -128,6 +128,13 @@ def test_leap_interleaved_rows(routes, n, d, ranecu, lane):
     assert routes("leap_packed", [(n, d, ranecu)]) == [[lane]]
 
 
+@pytest.mark.parametrize("n,d,ranecu,lane", [(65536, 24, 1, 1), (65536, 32, 1, 1), (131072, 24, 1, 1), (65500, 37, 1, 1),
+                                             (54848, 35, 1, 1), (65536, 8, 1, 0), (65536, 64, 1, 0), (44032, 32, 1, 0),
+                                             (98304, 32, 1, 0), (65536, 24, 0, 0)])
+def test_leap_interleaved_rows_of_few_draws(routes, n, d, ranecu, lane):
+    assert routes("leap_packed", [(n, d, ranecu)]) == [[lane]]
+
+
 # ----------------------------------------------------------------- the consumer
 GGL, XOR128, RANECU, DRAND48, RANNYU = 1, 2, 3, 7, 8
 
